@@ -16,7 +16,11 @@ CSRC = os.path.join(PKG, "csrc")
 OUT = os.path.join(PKG, "libvie.so")
 OBJ = os.path.join(ROOT, "_build")
 
-SOURCES = ["mvm.hip", "krylov.hip", "block_solver.hip", "fields.hip", "gmres.hip", "vie_api.cpp"]
+# Object of libvie -> its sources.  The product's kernels are compiled in
+# several translation units side by side and merged into one object.
+OBJECTS = {"mvm": ["mvm.hip", "zconv32.hip", "zconv64.hip"], "krylov": ["krylov.hip"],
+           "block_solver": ["block_solver.hip"], "fields": ["fields.hip"], "gmres": ["gmres.hip"],
+           "vie_api": ["vie_api.cpp"]}
 
 # Packed FP32 instructions are disabled for every HIP translation unit.
 FLAGS = ["--offload-arch=gfx950", "-O3", "-std=c++17", "-fPIC", "-I" + os.path.join(ROOT, "include"),
@@ -30,28 +34,29 @@ def _hipcc():
     return "hipcc"
 
 
-def _compile(src: str, verbose: bool) -> str:
-    obj = os.path.join(OBJ, os.path.splitext(src)[0] + ".o")
-    cmd = [_hipcc(), *FLAGS, "-x", "hip", "-c", os.path.join(CSRC, src), "-o", obj]
+def _run(cmd, what: str, verbose: bool) -> None:
     if verbose:
         print(" ".join(cmd), flush=True)
     r = subprocess.run(cmd, capture_output=True, text=True)
     if r.returncode != 0:
-        raise RuntimeError(f"hipcc failed for {src}:\n{r.stdout}\n{r.stderr}")
-    return obj
+        raise RuntimeError(f"{what} failed:\n{r.stdout}\n{r.stderr}")
 
 
 def build(verbose: bool = False) -> str:
-    os.makedirs(OBJ, exist_ok=True)
-    with cf.ThreadPoolExecutor(max_workers=min(len(SOURCES), os.cpu_count() or 1)) as ex:
-        objs = list(ex.map(lambda s: _compile(s, verbose), SOURCES))
+    parts = {}   # source -> object file
+    for name, srcs in OBJECTS.items():
+        d = OBJ if len(srcs) == 1 else os.path.join(OBJ, name)
+        os.makedirs(d, exist_ok=True)
+        parts.update({s: os.path.join(d, os.path.splitext(s)[0] + ".o") for s in srcs})
+    with cf.ThreadPoolExecutor(max_workers=min(len(parts), os.cpu_count() or 1)) as ex:
+        list(ex.map(lambda s: _run([_hipcc(), *FLAGS, "-x", "hip", "-c", os.path.join(CSRC, s), "-o", parts[s]],
+                                   f"hipcc for {s}", verbose), parts))
+    objs = [os.path.join(OBJ, name + ".o") for name in OBJECTS]
+    for (name, srcs), obj in zip(OBJECTS.items(), objs):
+        if len(srcs) > 1:
+            _run(["ld", "-r", *[parts[s] for s in srcs], "-o", obj], f"merging {name}", verbose)
     tmp = OUT + ".tmp"
-    cmd = [_hipcc(), "--offload-arch=gfx950", "-shared", "-fPIC", *objs, "-o", tmp]
-    if verbose:
-        print(" ".join(cmd), flush=True)
-    r = subprocess.run(cmd, capture_output=True, text=True)
-    if r.returncode != 0:
-        raise RuntimeError(f"link failed:\n{r.stdout}\n{r.stderr}")
+    _run([_hipcc(), "--offload-arch=gfx950", "-shared", "-fPIC", *objs, "-o", tmp], "link", verbose)
     os.replace(tmp, OUT)
     return OUT
 

@@ -24,6 +24,7 @@
 #include "api_lock.h"
 #include "fft_core.h"
 #include "krylov_dev.h"
+#include "zpass.h"
 
 namespace vie {
 
@@ -34,19 +35,6 @@ int smallest_fft_length(int min_len, bool xy) {
 }
 
 // ------------------------------------------------------------------ geometry
-constexpr int pow2_ceil(int v) {
-  int p = 1;
-  while (p < v) p *= 2;
-  return p;
-}
-constexpr int pow2_floor(int v) {
-  int p = 1;
-  while (p * 2 <= v) p *= 2;
-  return p;
-}
-constexpr int cmin(int a, int b) { return a < b ? a : b; }
-constexpr int cmax(int a, int b) { return a > b ? a : b; }
-
 template <typename R, int L>
 struct Geo {
   static constexpr int T = PlanInfo<L>::max_butterflies;  // threads per pencil
@@ -62,10 +50,6 @@ struct Geo {
   static constexpr int TC = cmin(T, cmax(1, 1024 / COLP));
 };
 
-__device__ __forceinline__ bool sys_active(const int* status, int s) {
-  return status == nullptr || status[s] == ST_ACTIVE;
-}
-
 // n / d by one multiply-high: m = ceil(2^32 / d) for d >= 2, m = 0 for d = 1.
 // With n = q d + r, n m / 2^32 = n / d + n (m - 2^32 / d) / 2^32 and the
 // second term is below n / 2^32, so the floor is q whenever n d < 2^32.
@@ -73,11 +57,6 @@ __device__ __forceinline__ bool sys_active(const int* status, int s) {
 // range (checked when they are launched).
 inline unsigned div_magic(int d) { return d <= 1 ? 0u : (unsigned)(((1ull << 32) + (unsigned)d - 1) / (unsigned)d); }
 __device__ __forceinline__ unsigned udiv_m(unsigned n, unsigned m) { return m ? __umulhi(n, m) : n; }
-
-template <typename R>
-__device__ __forceinline__ cx<R> czero() {
-  return mk<R>(R(0), R(0));
-}
 
 // ------------------------------------------------------------------ kernels
 template <typename R>
@@ -594,394 +573,7 @@ __global__ void __launch_bounds__((Geo<R, L>::TC * Geo<R, L>::COLP)) k_col(ColAr
   fft_pencil<R, L, G::TC, DIR>(ld, st, lds + p, G::COLP, t, valid, a.tw);
 }
 
-// Pass 3: z forward (nz -> LZ), spectral multiply, z inverse (LZ -> nz).
-//
-// The spectrum is stored for q in [0, L/2] per axis only; the other octants
-// are the same values with a sign (S_ij(L - q) = +-S_ij(q)).  An axis of
-// length L is covered by folds f in [0, nfold(L)); fold f stands for column
-// f (mirror 0) and column L - f (mirror 1), both using spectral index f.
-// For even L fold 0's mirror is the Nyquist column L/2 (spectral index L/2,
-// sign +); for odd L fold 0 has no mirror.  A workgroup takes one y-fold and
-// ZP consecutive x-folds and transforms all four mirror columns
-// (+-qx, +-qy) of the three components, so each spectrum value is loaded
-// once and applied to up to 8 points (+-qx, +-qy, qz and LZ - qz).
-__host__ __device__ constexpr int nfold(int L) { return (L % 2 == 0) ? L / 2 : (L + 1) / 2; }
-
-struct FoldCol {
-  int col;  // column index, -1 if absent
-  int sf;   // spectral (octant) index
-  int sg;   // parity sign for components odd in this axis
-};
-
-__device__ __forceinline__ FoldCol fold_col(int f, int m, int L) {
-  if (m == 0) return {f, f, 1};
-  if (f > 0) return {L - f, f, -1};
-  if ((L & 1) == 0 && L >= 2) return {L / 2, L / 2, 1};
-  return {-1, 0, 1};
-}
-
-// Element i of an array whose byte size is below 4 GiB: the byte offset is
-// formed in 32 bits, so the access can use a uniform base register plus a
-// 32-bit per-lane offset.
-template <typename T>
-__device__ __forceinline__ T* elem(T* base, unsigned i) {
-  return reinterpret_cast<T*>(reinterpret_cast<char*>(base) + i * (unsigned)sizeof(T));
-}
-template <typename T>
-__device__ __forceinline__ const T* elem(const T* base, unsigned i) {
-  return reinterpret_cast<const T*>(reinterpret_cast<const char*>(base) + i * (unsigned)sizeof(T));
-}
-
-// Workgroup b of n runs on XCD b % 8 (round-robin dispatch).  Renumber so
-// that each XCD takes one contiguous range of the logical order: work that
-// shares data then shares that XCD's L2.
-__device__ __forceinline__ int xcd_chunked(int b, int n) {
-  constexpr int NX = 8;
-  const int q = n / NX, r = n - q * NX;
-  const int x = b % NX, l = b / NX;
-  return x * q + min(x, r) + l;
-}
-
-// Logical row i -> qy in the order 0, 1, L-1, 2, L-2, ...: rows that share
-// an octant row of the spectra (qy and L - qy) are adjacent.
-__device__ __forceinline__ int mirror_paired_row(int i, int L) {
-  if (i == 0) return 0;
-  const int k = (i + 1) >> 1;
-  return (i & 1) ? k : L - k;
-}
-
-// Variant 0: one tile of ZP columns per workgroup, three components side by
-// side; each point loads its spectrum values.  Tiles run along mirror-paired
-// rows, chunked per XCD, so the four mirror columns that use one octant
-// spectrum value are transformed on one XCD close together in time and the
-// value is fetched from HBM about once.
-// Column-set variants (V = 0, 2, 3, 4): ZP columns per workgroup, TZ threads
-// per column and component, PF: spectrum values loaded into registers
-// before the data (their latency overlaps the forward transform).
-//   0: wide tiles (up to 1024 threads), max_butterflies threads per column
-//   2: wide tiles, min_butterflies rounded up to a power of two threads per
-//      column, prefetch (for L = 48: 4 threads, so a 16-column tile of the
-//      three components fills three whole wavefronts and each thread takes
-//      four radix-3 butterflies, where 3 threads leave a quarter of the
-//      third wavefront idle and take six butterflies, the last for one
-//      thread in three)
-//   3: one cache line of columns, min_butterflies threads, prefetch
-//   4: one cache line of columns, max_butterflies threads
-template <typename R, int LZ, int V>
-struct ZColGeo {
-  static constexpr int T = PlanInfo<LZ>::max_butterflies;
-  static constexpr int TB = V == 2 ? cmin(T, pow2_ceil(PlanInfo<LZ>::min_butterflies)) : PlanInfo<LZ>::min_butterflies;
-  static constexpr int ES = (int)sizeof(cx<R>);
-  static constexpr int LDS_ZP = cmax(1, (144 * 1024) / (3 * LZ * ES));
-  static constexpr int LINE = cmax(1, pow2_floor(cmin(LDS_ZP, 128 / ES)));
-  static constexpr int WIDE = cmax(1, pow2_floor(cmin(LDS_ZP, cmin(64, cmax(128 / ES, 1024 / (3 * T))))));
-  static constexpr int ZP = (V == 3 || V == 4) ? LINE : WIDE;
-  static constexpr int TZ = (V == 2 || V == 3) ? cmin(TB, cmax(1, 1024 / (3 * ZP)))
-                                               : cmin(T, pow2_floor(cmax(1, 1024 / (3 * ZP))));
-  static constexpr bool PF = V == 2 || V == 3;
-};
-
-// Variant 1 (mirror columns): geometry.
-template <typename R, int LZ>
-struct ZGeo {
-  static constexpr int T = PlanInfo<LZ>::max_butterflies;
-  static constexpr int ES = (int)sizeof(cx<R>);
-  static constexpr int ZP = cmax(1, pow2_floor(cmin(64, cmin(1024 / (3 * T), (144 * 1024) / (12 * LZ * ES)))));
-};
-
-template <typename R>
-struct ZArgs {
-  int nz, ly, lx;
-  int variant;   // 0, 2, 3, 4: column sets (ZColGeo); 1: mirror columns
-  int rooftop;   // spectral multiply of the rooftop discretisation (column sets only)
-  int64_t wstride, sstride;
-  cx<R>* work;
-  const cx<R>* spec;
-  const cx<R>* const* spec_tab;   // per-system spectra (null: spec + sys sstride)
-  const int* status;
-  const cx<R>* tw;
-};
-
-template <typename R, int LZ>
-__global__ void __launch_bounds__((3 * ZGeo<R, LZ>::T * ZGeo<R, LZ>::ZP)) k_zconv_mirror(ZArgs<R> a) {
-  using G = ZGeo<R, LZ>;
-  constexpr int T = G::T, ZP = G::ZP;
-  constexpr int SLOT = LZ * ZP;           // one (mirror, component) pencil set
-  __shared__ cx<R> lds[12 * SLOT];        // [mirror 4][component 3][qz][p]
-  const int lx = a.lx, ly = a.ly, nz = a.nz;
-  const int nfx = nfold(lx), nfy = nfold(ly);
-  const int xt = (nfx + ZP - 1) / ZP;
-  const int per_sys = nfy * xt;
-  const int sys = blockIdx.x / per_sys;
-  const int rr = blockIdx.x - sys * per_sys;
-  const int fy = rr / xt, ft = rr - fy * xt;
-  if (!sys_active(a.status, sys)) return;
-  const int comp = threadIdx.x / (T * ZP);
-  const int rem = threadIdx.x - comp * (T * ZP);
-  const int p = rem % ZP, t = rem / ZP;
-  const int fx = ft * ZP + p;
-  const bool pvalid = fx < nfx;
-  const int64_t plane = (int64_t)ly * lx;
-  cx<R>* wsys = a.work + sys * a.wstride + (int64_t)comp * nz * plane;
-
-  // forward along z of the four mirror columns, into LDS
-#pragma unroll
-  for (int m = 0; m < 4; ++m) {
-    const FoldCol cxm = fold_col(fx, m & 1, lx), cym = fold_col(fy, m >> 1, ly);
-    const bool valid = pvalid && cxm.col >= 0 && cym.col >= 0;
-    cx<R>* base = wsys + (valid ? (int64_t)cym.col * lx + cxm.col : 0);
-    cx<R>* slot = lds + (m * 3 + comp) * SLOT + p;
-    auto ldg = [&](int n) -> cx<R> { return n < nz ? base[n * plane] : czero<R>(); };
-    auto sts = [&](int k, cx<R> v) { slot[k * ZP] = v; };
-    fft_pencil<R, LZ, T, -1, false, true>(ldg, sts, slot, ZP, t, valid, a.tw);
-  }
-
-  // Q = S X at every point of the four columns; one spectrum load per
-  // (fold x, fold y, fold z), reused for its mirrors
-  const int64_t ox = lx / 2 + 1, oy = ly / 2 + 1;
-  const int64_t oct = ox * oy * (LZ / 2 + 1);
-  const cx<R>* spec = a.spec_tab ? a.spec_tab[sys] : a.spec + sys * a.sstride;
-  constexpr int NFZ = nfold(LZ);
-  for (int i = threadIdx.x; i < NFZ * ZP; i += 3 * T * ZP) {
-    const int fz = i / ZP, pp = i - fz * ZP;
-    const int fxx = ft * ZP + pp;
-    if (fxx >= nfx) continue;
-    int64_t o_prev = -1;
-    cx<R> sxx, sxy, sxz, syy, syz, szz;
-#pragma unroll
-    for (int mz = 0; mz < 2; ++mz) {
-      const FoldCol czm = fold_col(fz, mz, LZ);
-      if (czm.col < 0) continue;
-#pragma unroll
-      for (int m = 0; m < 4; ++m) {
-        const FoldCol cxm = fold_col(fxx, m & 1, lx), cym = fold_col(fy, m >> 1, ly);
-        if (cxm.col < 0 || cym.col < 0) continue;
-        const int64_t o = ((int64_t)czm.sf * oy + cym.sf) * ox + cxm.sf;
-        if (o != o_prev) {
-          sxx = spec[o];
-          sxy = spec[oct + o];
-          sxz = spec[2 * oct + o];
-          syy = spec[3 * oct + o];
-          syz = spec[4 * oct + o];
-          szz = spec[5 * oct + o];
-          o_prev = o;
-        }
-        const R gxy = R(cxm.sg * cym.sg), gxz = R(cxm.sg * czm.sg), gyz = R(cym.sg * czm.sg);
-        const cx<R> axy = gxy * sxy, axz = gxz * sxz, ayz = gyz * syz;
-        cx<R>* e = lds + m * 3 * SLOT + czm.col * ZP + pp;
-        const cx<R> X = e[0], Y = e[SLOT], Z = e[2 * SLOT];
-        e[0] = sxx * X + axy * Y + axz * Z;
-        e[SLOT] = axy * X + syy * Y + ayz * Z;
-        e[2 * SLOT] = axz * X + ayz * Y + szz * Z;
-      }
-    }
-  }
-  __syncthreads();
-
-  // inverse along z, cropped to nz, back to HBM
-#pragma unroll
-  for (int m = 0; m < 4; ++m) {
-    const FoldCol cxm = fold_col(fx, m & 1, lx), cym = fold_col(fy, m >> 1, ly);
-    const bool valid = pvalid && cxm.col >= 0 && cym.col >= 0;
-    cx<R>* base = wsys + (valid ? (int64_t)cym.col * lx + cxm.col : 0);
-    cx<R>* slot = lds + (m * 3 + comp) * SLOT + p;
-    auto lds_ld = [&](int n) -> cx<R> { return slot[n * ZP]; };
-    auto stg = [&](int k, cx<R> v) {
-      if (k < nz) base[k * plane] = v;
-    };
-    fft_pencil<R, LZ, T, +1, true, false>(lds_ld, stg, slot, ZP, t, valid, a.tw);
-  }
-}
-
-// K = 0: the collocated dyadic multiply (six octant spectra of the symmetric
-// tensor).  K = 1: the rooftop discretisation, whose spectral operator is
-// G'(q) (X_c - conj(b_c) sum_j b_j X_j) with G' = k0^2 dV FFT(g~) (one even
-// octant spectrum) and b_j = (1 - exp(-2 pi i q_j / L_j)) / (k0 d_j), the
-// symbol of the cell divergence of face values; -conj(b_c) is the symbol of
-// the face gradient of cell values.  The spectrum buffer holds the octant of
-// G' followed by the full-length tables b_x[lx], b_y[ly], b_z[lz].
-template <typename R, int LZ, int V, int K>
-__global__ void __launch_bounds__((3 * ZColGeo<R, LZ, V>::TZ * ZColGeo<R, LZ, V>::ZP)) k_zconv_col(ZArgs<R> a) {
-  using G = ZColGeo<R, LZ, V>;
-  constexpr int T = G::TZ, ZP = G::ZP;
-  constexpr int NT = 3 * T * ZP;
-  constexpr int HZ = LZ / 2;
-  constexpr int NFT = NT / ZP;                    // fold walkers per column
-  constexpr int NF = (HZ + 1 + NFT - 1) / NFT;    // folds per walker
-  __shared__ cx<R> lds[3 * LZ * ZP];
-  const int cols = a.ly * a.lx;
-  const int tiles = (cols + ZP - 1) / ZP;
-  // Tile-major logical order (the grid is tiles x systems): each XCD takes
-  // a contiguous range of tiles of every system, so the systems still
-  // active are spread over all XCDs whichever they are, and the group's
-  // shared spectrum columns of a tile are reused from that XCD's L2 by the
-  // consecutive workgroups of the other systems.
-  const int nsys = (int)gridDim.x / tiles;
-  const int g = __builtin_amdgcn_readfirstlane(xcd_chunked(blockIdx.x, gridDim.x));   // uniform
-  const int tile = g / nsys, sys = g - tile * nsys;
-  if (!sys_active(a.status, sys)) return;
-  const int comp = threadIdx.x / (T * ZP);
-  const int rem = threadIdx.x - comp * (T * ZP);
-  const int p = rem % ZP, t = rem / ZP;
-  const int col = tile * ZP + p;   // logical column
-  const bool valid = col < cols;
-  // element offsets in 32 bits from the system's base (one system's work
-  // buffer holds < 2^31 elements), so loads use a uniform base + offset
-  const unsigned plane = (unsigned)a.ly * (unsigned)a.lx;
-  unsigned pcol = 0;               // its place in the plane
-  if (valid) {
-    const int i = col / a.lx;
-    pcol = (unsigned)(mirror_paired_row(i, a.ly) * a.lx + (col - i * a.lx));
-  }
-  cx<R>* const wsys = a.work + sys * a.wstride;
-  const unsigned coff = (unsigned)comp * (unsigned)a.nz * plane + pcol;
-  cx<R>* slot = lds + comp * LZ * ZP + p;
-  const int nz = a.nz;
-
-  // The multiply's view: a thread keeps one column (qx, qy) and walks the
-  // z-folds fz = j, j + NFT, ...: each spectrum value serves qz = fz and
-  // qz = LZ - fz.
-  const int lx = a.lx, ly = a.ly;
-  const int hx = lx / 2, hy = ly / 2;
-  const int64_t ox = hx + 1, oy = hy + 1;
-  const int64_t oct = ox * oy * (HZ + 1);
-  const int pp = threadIdx.x % ZP, j0 = threadIdx.x / ZP;
-  const int c2 = tile * ZP + pp;
-  const bool cvalid = c2 < cols;
-  R sx = R(1), sy = R(1);
-  const cx<R>* const sp = a.spec_tab ? a.spec_tab[sys] : a.spec + sys * a.sstride;
-  unsigned soff = 0;
-  cx<R> bx = czero<R>(), by = czero<R>();   // K = 1: difference symbols of the column
-  const unsigned oct32 = (unsigned)oct, fzs = (unsigned)(oy * ox);
-  if (cvalid) {
-    const int i2 = c2 / lx;
-    const int qy = mirror_paired_row(i2, ly), qx = c2 - i2 * lx;
-    const int fx = qx <= hx ? qx : lx - qx, fy = qy <= hy ? qy : ly - qy;
-    sx = qx <= hx ? R(1) : R(-1);
-    sy = qy <= hy ? R(1) : R(-1);
-    soff = (unsigned)(fy * ox + fx);
-    if constexpr (K == 1) {
-      bx = *elem(sp, oct32 + (unsigned)qx);
-      by = *elem(sp, oct32 + (unsigned)(lx + qy));
-    }
-  }
-  constexpr int NS = K == 1 ? 3 : 6;
-  // K = 0: spectrum values (xx, xy, xz, yy, yz, zz, parity signs of qx, qy
-  // applied); K = 1: G'(fz), b_z(fz), b_z(LZ - fz)
-  auto spec_at = [&](int fz, cx<R>* sv) {
-    const unsigned o = soff + (unsigned)fz * fzs;
-    if constexpr (K == 1) {
-      const unsigned bz0 = oct32 + (unsigned)(lx + ly);
-      sv[0] = *elem(sp, o);
-      sv[1] = *elem(sp, bz0 + (unsigned)fz);
-      sv[2] = *elem(sp, bz0 + (unsigned)(fz == 0 ? 0 : LZ - fz));
-    } else {
-      sv[0] = *elem(sp, o);
-      sv[1] = (sx * sy) * *elem(sp, oct32 + o);
-      sv[2] = sx * *elem(sp, 2 * oct32 + o);
-      sv[3] = *elem(sp, 3 * oct32 + o);
-      sv[4] = sy * *elem(sp, 4 * oct32 + o);
-      sv[5] = *elem(sp, 5 * oct32 + o);
-    }
-  };
-  cx<R> pre[G::PF ? NF : 1][NS];
-  if constexpr (G::PF) {
-#pragma unroll
-    for (int f = 0; f < NF; ++f) {
-      const int fz = j0 + f * NFT;
-      if (cvalid && fz <= HZ) spec_at(fz, pre[f]);
-    }
-  }
-
-  // forward along z into the component's LDS slot
-  // first-stage element n = t + (a constant of the unrolled stage): offsets
-  // split into a per-thread part and a uniform part
-  const unsigned toff = coff + (unsigned)t * plane;
-  auto ldg = [&](int n) -> cx<R> {
-    return n < nz ? *elem(wsys, toff + (unsigned)(n - t) * plane) : czero<R>();
-  };
-  auto sts = [&](int k, cx<R> v) { slot[k * ZP] = v; };
-  fft_pencil<R, LZ, T, -1, false, true>(ldg, sts, slot, ZP, t, valid, a.tw);
-
-  // Q(q) = S(q) X(q), S symmetric 3x3 from the octant with parity signs
-  if constexpr (K == 1) if (cvalid) {
-    cx<R>* e0 = lds + pp;
-    const cx<R> cbx = conj(bx), cby = conj(by);
-    auto roof = [&](cx<R>* e, cx<R> gq, cx<R> bz) {
-      const cx<R> X = e[0], Y = e[LZ * ZP], Z = e[2 * LZ * ZP];
-      const cx<R> d = bx * X + by * Y + bz * Z;   // divergence
-      e[0] = gq * (X - cbx * d);
-      e[LZ * ZP] = gq * (Y - cby * d);
-      e[2 * LZ * ZP] = gq * (Z - conj(bz) * d);
-    };
-#pragma unroll
-    for (int f = 0; f < NF; ++f) {
-      const int fz = j0 + f * NFT;
-      if (fz > HZ) break;
-      cx<R> sl[NS];
-      const cx<R>* sv = sl;
-      if constexpr (G::PF)
-        sv = pre[f];
-      else
-        spec_at(fz, sl);
-      roof(e0 + fz * ZP, sv[0], sv[1]);
-      const int qz2 = LZ - fz;
-      if (fz > 0 && qz2 != fz) roof(e0 + qz2 * ZP, sv[0], sv[2]);
-    }
-  }
-  if constexpr (K == 0) if (cvalid) {
-    cx<R>* e0 = lds + pp;
-#pragma unroll
-    for (int f = 0; f < NF; ++f) {
-      const int fz = j0 + f * NFT;
-      if (fz > HZ) break;
-      cx<R> sl[NS];
-      const cx<R>* sv = sl;
-      if constexpr (G::PF)
-        sv = pre[f];
-      else
-        spec_at(fz, sl);
-      const cx<R> sxx = sv[0], sxy = sv[1], sxz = sv[2], syy = sv[3], syz = sv[4], szz = sv[5];
-      {
-        cx<R>* e = e0 + fz * ZP;   // qz = fz: sz = +1
-        const cx<R> X = e[0], Y = e[LZ * ZP], Z = e[2 * LZ * ZP];
-        e[0] = sxx * X + sxy * Y + sxz * Z;
-        e[LZ * ZP] = sxy * X + syy * Y + syz * Z;
-        e[2 * LZ * ZP] = sxz * X + syz * Y + szz * Z;
-      }
-      const int qz2 = LZ - fz;
-      if (fz > 0 && qz2 != fz) {   // qz = LZ - fz: sz = -1
-        cx<R>* e = e0 + qz2 * ZP;
-        const cx<R> X = e[0], Y = e[LZ * ZP], Z = e[2 * LZ * ZP];
-        e[0] = sxx * X + sxy * Y - sxz * Z;
-        e[LZ * ZP] = sxy * X + syy * Y - syz * Z;
-        e[2 * LZ * ZP] = szz * Z - sxz * X - syz * Y;
-      }
-    }
-  }
-  __syncthreads();
-  // inverse along z, cropped to nz
-  auto lds_ld = [&](int n) -> cx<R> { return slot[n * ZP]; };
-  auto stg = [&](int k, cx<R> v) {
-    if (k < nz) *elem(wsys, toff + (unsigned)(k - t) * plane) = v;
-  };
-  fft_pencil<R, LZ, T, +1, true, false>(lds_ld, stg, slot, ZP, t, valid, a.tw);
-}
-
 // ------------------------------------------------------------------ launchers
-#define VIE_L_CASES(F)                                                                                    \
-  F(1) F(2) F(3) F(4) F(6) F(8) F(12) F(16) F(24) F(32) F(36) F(48) F(64) F(72) F(96) F(128) F(144) F(192) F(256) \
-      F(288) F(384) F(512)
-
-[[noreturn]] static void bad_length(const char* what, int L) {
-  throw std::runtime_error(std::string("unsupported FFT length for ") + what + ": " + std::to_string(L));
-}
-
-static void check_launch(const char* what) {
-  hipError_t e = hipGetLastError();
-  if (e != hipSuccess) throw std::runtime_error(std::string("kernel launch failed (") + what + "): " + hipGetErrorString(e));
-}
-
 template <typename R>
 static void launch_row_fwd(int L, const RowArgs<R>& a, int nsys, hipStream_t s) {
   switch (L) {
@@ -1035,49 +627,6 @@ static void launch_col(int L, const ColArgs<R>& a, hipStream_t s) {
       bad_length("column pass", L);
   }
   check_launch("column pass");
-}
-
-constexpr int kZVariants = kZPassVariants;   // 0, 2, 3, 4: column sets; 1: mirror columns
-
-template <typename R, int L, int V>
-static void launch_zcol(const ZArgs<R>& a, int nsys, hipStream_t s) {
-  using G = ZColGeo<R, L, V>;
-  const int cols = a.ly * a.lx;
-  const int blocks = ((cols + G::ZP - 1) / G::ZP) * nsys;
-  if (a.rooftop)
-    hipLaunchKernelGGL((k_zconv_col<R, L, V, 1>), dim3(blocks), dim3(3 * G::TZ * G::ZP), 0, s, a);
-  else
-    hipLaunchKernelGGL((k_zconv_col<R, L, V, 0>), dim3(blocks), dim3(3 * G::TZ * G::ZP), 0, s, a);
-}
-
-template <typename R>
-static void launch_zconv(int L, const ZArgs<R>& a, int nsys, hipStream_t s) {
-  const int nfy = nfold(a.ly), nfx = nfold(a.lx);
-  switch (L) {
-#define C(l)                                                                                      \
-  case l: {                                                                                       \
-    if (a.variant == 1) {                                                                         \
-      if (a.rooftop) throw std::runtime_error("z pass: no mirror-column variant for rooftop spectra"); \
-      using G = ZGeo<R, l>;                                                                       \
-      const int blocks = nfy * ((nfx + G::ZP - 1) / G::ZP) * nsys;                                \
-      hipLaunchKernelGGL((k_zconv_mirror<R, l>), dim3(blocks), dim3(3 * G::T * G::ZP), 0, s, a);  \
-    } else if (l < 32 || a.variant == 0) {                                                        \
-      launch_zcol<R, l, 0>(a, nsys, s);                                                           \
-    } else if (a.variant == 2) {                                                                  \
-      launch_zcol<R, l, (l < 32 ? 0 : 2)>(a, nsys, s);                                            \
-    } else if (a.variant == 3) {                                                                  \
-      launch_zcol<R, l, (l < 32 ? 0 : 3)>(a, nsys, s);                                            \
-    } else {                                                                                      \
-      launch_zcol<R, l, (l < 32 ? 0 : 4)>(a, nsys, s);                                            \
-    }                                                                                             \
-    break;                                                                                        \
-  }
-    VIE_L_CASES(C)
-#undef C
-    default:
-      bad_length("z pass", L);
-  }
-  check_launch("z pass");
 }
 
 #define VIE_PLANE_CASES(F) F(8) F(12) F(16) F(24) F(32) F(48) F(64)
@@ -1295,7 +844,7 @@ int tune_zpass(const MvmBatch<R>& b, hipStream_t s, float* ms_out) {
   }
   float best = 1e30f;
   int best_v = 0;
-  for (int v = 0; v < kZVariants; ++v) {
+  for (int v = 0; v < kZPassVariants; ++v) {
     if (v >= 2 && b.lz < 32) break;   // short columns: variants 0 and 1 only
     if (v == 1 && b.rooftop) continue;   // column sets only
     ZArgs<R> za{};
