@@ -199,10 +199,11 @@ void block_solve(const BlockSolveArgs& a, int lx, int lz, hipStream_t s);
 
 // Far field F(rhat) = (I - rhat rhat) sum_n P_n dV exp(+j k0 rhat . r_n)
 // for ndir directions (rhat: device, 3 doubles each; F: device, 3 c128 each).
-// part: device scratch of 6 far_field_chunks(nx ny nz) doubles per direction.
+// part: device scratch of far_field_scratch(nx, ny, nz, ndir) doubles (tables
+// and partial sums; never more than far_field_scratch_doubles()).
 // faces: P holds rooftop face unknowns (component c at its face centre, half
 // a cell along axis c from the voxel centre).
-int64_t far_field_chunks(int64_t nv);
+int64_t far_field_scratch(int nx, int ny, int nz, int ndir);
 // The far field's fixed scratch array (for the entry point that allocates
 // nothing): its capacity in doubles, and its address on the current device
 // (looked up once per device at set-up; throws on failure).

@@ -391,9 +391,15 @@ struct vie_problem {
   std::unique_ptr<vie_problem> replica;
   int replica_nrhs = 0;
   size_t replica_bytes = 0;
+  // far field: device workspace and pinned host staging kept from call to
+  // call (bounded by kFarKeep; contexts with a memory budget keep neither)
+  DevBuf far_dev;
+  void* far_host = nullptr;
+  size_t far_host_bytes = 0;
 
   ~vie_problem() {
     ApiShared api;
+    if (far_host) (void)hipHostFree(far_host);
     for (auto& G : groups)
       for (auto g : G.graph)
         if (g) (void)hipGraphExecDestroy(g);
@@ -2649,6 +2655,9 @@ vie_status vie_total_field_box(vie_problem* p, int32_t precision, const void* po
 }
 
 extern "C++" {
+// Far-field workspace a problem may keep: the scratch's 8 MiB and room for
+// the directions and results of about 100 000.
+constexpr size_t kFarKeep = size_t(16) << 20;
 static void far_field_host(vie_problem* p, const void* pol_dev, int32_t n_dir, const double* rhat,
                            std::vector<c128>& F, hipStream_t s) {
   if (!p || !pol_dev || !rhat) fail(VIE_EINVAL, "problem, pol and rhat are required");
@@ -2661,15 +2670,37 @@ static void far_field_host(vie_problem* p, const void* pol_dev, int32_t n_dir, c
   }
   set_device(p->ctx);
   const vie_grid& g = p->g;
-  const int64_t nchunk = vie::far_field_chunks(p->nv);
-  DevBuf dr(3 * (size_t)n_dir * sizeof(double)), part(6 * (size_t)n_dir * nchunk * sizeof(double)),
-      dF(3 * (size_t)n_dir * sizeof(c128));
-  hip_check(hipMemcpyAsync(dr.p, rhat, dr.bytes, hipMemcpyHostToDevice, s), "upload rhat");
-  vie::far_field((const c128*)pol_dev, g.nx, g.ny, g.nz, g.dx, g.dy, g.dz, p->k0, dr.as<double>(), n_dir,
-                 part.as<double>(), dF.as<c128>(), s, p->rooftop);
+  const size_t rb = 3 * (size_t)n_dir * sizeof(double), fb = 3 * (size_t)n_dir * sizeof(c128);
+  const size_t pb = (size_t)vie::far_field_scratch(g.nx, g.ny, g.nz, n_dir) * sizeof(double);
+  const size_t r_at = (fb + 255) / 256 * 256, p_at = r_at + (rb + 255) / 256 * 256;   // F, rhat, scratch
+  const bool keep = p->ctx->budget == 0 && p_at + pb <= kFarKeep;
+  DevBuf once;
+  if (!keep)
+    once.alloc(p_at + pb);
+  else if (p->far_dev.bytes < p_at + pb)
+    p->far_dev.alloc(p_at + pb);   // every call waits for its work: the old one is idle
+  char* dev = (keep ? p->far_dev : once).as<char>();
+  if (keep && p->far_host_bytes < rb + fb) {
+    ApiShared api;
+    if (p->far_host) (void)hipHostFree(p->far_host);
+    p->far_host_bytes = 0;
+    if (hipHostMalloc(&p->far_host, rb + fb) == hipSuccess) {
+      p->far_host_bytes = rb + fb;
+    } else {
+      p->far_host = nullptr;
+      (void)hipGetLastError();
+    }
+  }
+  const bool pinned = keep && p->far_host_bytes >= rb + fb;
   F.resize(3 * (size_t)n_dir);
-  hip_check(hipMemcpyAsync(F.data(), dF.p, dF.bytes, hipMemcpyDeviceToHost, s), "download F");
+  if (pinned) std::memcpy((char*)p->far_host + fb, rhat, rb);
+  hip_check(hipMemcpyAsync(dev + r_at, pinned ? (const char*)p->far_host + fb : (const char*)rhat, rb, hipMemcpyHostToDevice, s),
+            "upload rhat");
+  vie::far_field((const c128*)pol_dev, g.nx, g.ny, g.nz, g.dx, g.dy, g.dz, p->k0, (const double*)(dev + r_at), n_dir,
+                 (double*)(dev + p_at), (c128*)dev, s, p->rooftop);
+  hip_check(hipMemcpyAsync(pinned ? p->far_host : (void*)F.data(), dev, fb, hipMemcpyDeviceToHost, s), "download F");
   hip_check(hipStreamSynchronize(s), "far field");
+  if (pinned) std::memcpy(F.data(), p->far_host, fb);
 }
 }  // extern "C++"
 
@@ -2690,7 +2721,7 @@ vie_status vie_far_field_noalloc(vie_problem* p, const void* pol_dev, int32_t n_
   return guarded([&]() -> vie_status {
     if (!p || !pol_dev || !rhat_dev || !f_dev) fail(VIE_EINVAL, "problem, pol, rhat and f are required");
     if (n_dir < 1) fail(VIE_EINVAL, "n_dir must be >= 1");
-    const int64_t nchunk = vie::far_field_chunks(p->nv);
+    const int64_t nchunk = (p->nv + 2047) / 2048;
     if ((int64_t)n_dir * nchunk * 6 > vie::far_field_scratch_doubles())
       fail(VIE_EINVAL, "n_dir * ceil(nx ny nz / 2048) * 6 exceeds the fixed scratch of 1048576 doubles (use "
                        "vie_far_field, or fewer directions per call)");
