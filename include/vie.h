@@ -175,10 +175,10 @@ typedef struct {
   int64_t footprint_bytes;    /* device memory held by the problem */
   int32_t n_block_solver_groups;  /* groups solved one workgroup per block */
   int32_t zpass_variant[2];   /* z-pass kernel picked for the full-grid product [FP64, MIXED] */
-  float zpass_tune_ms[2][5];  /* autotuner time per z-pass variant (3 runs; -1 = not timed) */
+  float zpass_tune_ms[2][5];  /* time per z-pass variant (-1 = not timed: variants are picked by shape) */
   int32_t plane_variant[2];   /* plane-kernel variant picked for the full-grid product [FP64, MIXED]
                                  (0 when its transforms are not square and small enough) */
-  float plane_tune_ms[2][3];  /* autotuner time per plane variant (3 forward + inverse pairs; -1 = not timed) */
+  float plane_tune_ms[2][3];  /* time per plane variant (-1 = not timed: variants are picked by shape) */
 } vie_problem_info;
 
 /* One shape group of a block plan: blocks whose bounding boxes share FFT
@@ -268,7 +268,7 @@ vie_status vie_problem_get_info(const vie_problem* p, vie_problem_info* info);
 /* Pins the z-pass kernel variant (0-4; 1 = mirror columns; lengths below
  * 32 use 0 for 2-4) of every FFT product of
  * the problem in one precision, full-grid and block products alike; -1
- * restores the autotuned choice.  For kernel studies and a reproducible
+ * restores the choice by shape.  For kernel studies and a reproducible
  * kernel choice: the variants compute the same transform (results agree to
  * rounding; tested).  Synchronises the device; call it while no work of the
  * problem is in flight.  Errors: VIE_EINVAL for a bad precision or
@@ -279,7 +279,7 @@ vie_status vie_problem_set_zpass(vie_problem* p, int32_t precision, int32_t vari
  * precision (products whose x and y lengths are equal and at most 64 run
  * the x and y transforms of a z-plane in one kernel; the variants differ in
  * the planes one workgroup takes: 0 as many as 48 KB of LDS hold, at most
- * 16; 1 at most two; 2 one); -1 restores the autotuned choice.  Same
+ * 16; 1 at most two; 2 one); -1 restores the choice by shape.  Same
  * transform, results agree to rounding (tested).  Synchronises the device;
  * call it while no work of the problem is in flight.  Errors: VIE_EINVAL
  * for a bad precision or variant. */
@@ -332,7 +332,7 @@ vie_status vie_matvec_profile(vie_problem* p, int32_t precision, const void* x_d
  * `reps` times on `stream` with HIP events around each of its passes (those
  * of vie_matvec_profile; passes 2 and 4 are empty for groups on the fused
  * plane kernels) and writes the mean duration of each pass in milliseconds
- * to pass_ms[0..4].  Kernels, grid and tuned variant are those of the inner
+ * to pass_ms[0..4].  Kernels, grid and variant are those of the inner
  * solves; the pass-1 and pass-5 kernels run without the fused vector
  * updates.  Uses and overwrites the problem's inner solver state: call it
  * between solves.  Synchronises the stream.  Errors: VIE_EINVAL for a bad

@@ -156,10 +156,65 @@ struct PlanInfo {
 
 // ---------------------------------------------------------------- pipeline
 // Twiddle table tw[t] = exp(-2 pi i t / L), t < L, in HBM (shared, cached).
+//
+// A thread's twiddles depend on its place in the pencil only, so they are
+// fetched once, before the pencil's data, where the registers allow it
+// (TwRegs): loaded at their use they put one more trip to the L2 on the path
+// of every stage, and again for every pencil a workgroup takes in turn.  Up to
+// 32 registers are spent on them; longer plans load them at their use.
+template <class Rad, int L, int T, int P>
+struct TwCount {
+  static constexpr int value = 0;
+};
+template <int RAD, int... Rest, int L, int T, int P>
+struct TwCount<Radices<RAD, Rest...>, L, T, P> {
+  static constexpr int here = P > 1 ? (RAD - 1) * ((L / RAD + T - 1) / T) : 0;
+  static constexpr int value = here + TwCount<Radices<Rest...>, L, T, P * RAD>::value;
+};
+
+template <typename R, int L, int T, bool HOLD = true>
+struct TwRegs {
+  static constexpr int count = TwCount<typename Plan<L>::type, L, T, 1>::value;
+  static constexpr bool held = HOLD && count * (int)sizeof(cx<R>) <= 32 * 4;
+  const cx<R>* __restrict__ tab;
+  cx<R> w[held && count > 0 ? count : 1];
+
+  template <int P, int AT, int RAD, int... Rest>
+  __device__ __forceinline__ void fetch(int t, Radices<RAD, Rest...>) {
+    constexpr int NPT = (L / RAD + T - 1) / T;
+    if constexpr (P > 1) {
+#pragma unroll
+      for (int q = 0; q < NPT; ++q) {
+        const int k = (t + q * T) % P;
+#pragma unroll
+        for (int m = 1; m < RAD; ++m) w[AT + q * (RAD - 1) + m - 1] = tab[(unsigned)(m * k * (L / (P * RAD)))];
+      }
+    }
+    if constexpr (sizeof...(Rest) > 0) fetch<P * RAD, AT + (P > 1 ? NPT * (RAD - 1) : 0)>(t, Radices<Rest...>{});
+  }
+  // t: the thread's place in its pencil
+  __device__ __forceinline__ TwRegs(const cx<R>* __restrict__ tw, int t) : tab(tw) {
+    if constexpr (held && count > 0) fetch<1, 0>(t, typename Plan<L>::type{});
+  }
+  // twiddle m of butterfly t + q T in the stage whose twiddles start at AT
+  template <int AT, int RAD, int P>
+  __device__ __forceinline__ cx<R> at(int q, int m, int k) const {
+    if constexpr (held)
+      return w[AT + q * (RAD - 1) + m - 1];
+    else
+      return tab[(unsigned)(m * k * (L / (P * RAD)))];   // unsigned 32-bit offset from a uniform base
+  }
+};
+
+// v w (forward) or v conj(w), with its fused operations spelled out: kernels
+// that hold their twiddles and kernels that load them agree bit for bit, which
+// they need not when the compiler chooses what to contract.
+__device__ __forceinline__ float fma1(float a, float b, float c) { return __builtin_fmaf(a, b, c); }
+__device__ __forceinline__ double fma1(double a, double b, double c) { return __builtin_fma(a, b, c); }
 template <int DIR, typename R>
-__device__ __forceinline__ cx<R> twiddle(const cx<R>* __restrict__ tw, int idx) {
-  cx<R> w = tw[(unsigned)idx];   // unsigned 32-bit offset from a uniform base
-  return DIR < 0 ? w : conj(w);
+__device__ __forceinline__ cx<R> twiddled(cx<R> v, cx<R> w) {
+  const R p = v.y * w.y, q = v.x * w.y;
+  return DIR < 0 ? mk<R>(fma1(v.x, w.x, -p), fma1(v.y, w.x, q)) : mk<R>(fma1(v.x, w.x, p), fma1(v.y, w.x, -q));
 }
 
 // One stage.  Threads t < T of a pencil cooperate; `lds` points at element 0
@@ -168,10 +223,10 @@ __device__ __forceinline__ cx<R> twiddle(const cx<R>* __restrict__ tw, int idx) 
 // LDLDS: the loader reads this pencil's LDS slot; STLDS: the storer writes
 // it.  Then the first (last) stage separates its reads from its writes by a
 // barrier, since the transform runs in place in the slot.
-template <typename R, int L, int T, int DIR, int RAD, int P, bool FIRST, bool LAST, bool LDLDS, bool STLDS,
-          class Load, class Store>
+template <typename R, int L, int T, int DIR, int RAD, int P, int AT, bool FIRST, bool LAST, bool LDLDS, bool STLDS,
+          class Load, class Store, bool HOLD>
 __device__ __forceinline__ void fft_stage(Load& ld, Store& st, cx<R>* lds, int ls, int t, bool tvalid,
-                                          const cx<R>* __restrict__ tw) {
+                                          const TwRegs<R, L, T, HOLD>& tw) {
   constexpr int NB = L / RAD;
   constexpr int NPT = (NB + T - 1) / T;
   constexpr bool READS_SLOT = !FIRST || LDLDS;
@@ -198,9 +253,8 @@ __device__ __forceinline__ void fft_stage(Load& ld, Store& st, cx<R>* lds, int l
     if (tvalid && (NB % T == 0 || b < NB)) {
       const int k = (P == 1) ? 0 : (b % P);
       if constexpr (P > 1) {
-        constexpr int TS = L / (P * RAD);
 #pragma unroll
-        for (int m = 1; m < RAD; ++m) v[q][m] = v[q][m] * twiddle<DIR>(tw, m * k * TS);
+        for (int m = 1; m < RAD; ++m) v[q][m] = twiddled<DIR>(v[q][m], tw.template at<AT, RAD, P>(q, m, k));
       }
       dft<RAD, DIR>(v[q]);
       const int j = (b - k) * RAD + k;
@@ -216,30 +270,40 @@ __device__ __forceinline__ void fft_stage(Load& ld, Store& st, cx<R>* lds, int l
   if constexpr (WRITES_SLOT) __syncthreads();
 }
 
-template <typename R, int L, int T, int DIR, int P, bool FIRST, bool LDLDS, bool STLDS, class Load, class Store,
-          int RAD, int... Rest>
+template <typename R, int L, int T, int DIR, int P, int AT, bool FIRST, bool LDLDS, bool STLDS, class Load, class Store,
+          bool HOLD, int RAD, int... Rest>
 __device__ __forceinline__ void fft_stages(Load& ld, Store& st, cx<R>* lds, int ls, int t, bool tvalid,
-                                           const cx<R>* __restrict__ tw, Radices<RAD, Rest...>) {
+                                           const TwRegs<R, L, T, HOLD>& tw, Radices<RAD, Rest...>) {
   constexpr bool LAST = sizeof...(Rest) == 0;
-  fft_stage<R, L, T, DIR, RAD, P, FIRST, LAST, LDLDS, STLDS>(ld, st, lds, ls, t, tvalid, tw);
+  constexpr int NEXT = AT + (P > 1 ? (RAD - 1) * ((L / RAD + T - 1) / T) : 0);
+  fft_stage<R, L, T, DIR, RAD, P, AT, FIRST, LAST, LDLDS, STLDS>(ld, st, lds, ls, t, tvalid, tw);
   if constexpr (!LAST)
-    fft_stages<R, L, T, DIR, P * RAD, false, LDLDS, STLDS>(ld, st, lds, ls, t, tvalid, tw, Radices<Rest...>{});
+    fft_stages<R, L, T, DIR, P * RAD, NEXT, false, LDLDS, STLDS>(ld, st, lds, ls, t, tvalid, tw, Radices<Rest...>{});
 }
 
 // Transform one pencil of length L: x_n = ld(n) (n < L) -> st(k, X_k).
 // Threads t in [0, T) of the pencil take part; tvalid = false threads still
 // hit the barriers but touch no data.  The pencil's LDS slot is the exchange
 // buffer between stages; see fft_stage for LDLDS / STLDS.
-template <typename R, int L, int T, int DIR, bool LDLDS = false, bool STLDS = false, class Load, class Store>
+template <typename R, int L, int T, int DIR, bool LDLDS = false, bool STLDS = false, class Load, class Store,
+          bool HOLD>
 __device__ __forceinline__ void fft_pencil(Load ld, Store st, cx<R>* lds, int ls, int t, bool tvalid,
-                                           const cx<R>* __restrict__ tw) {
+                                           const TwRegs<R, L, T, HOLD>& tw) {
   using rad = typename Plan<L>::type;
   if constexpr (RadInfo<rad>::nstages == 0) {
     if (tvalid && t == 0) st(0, ld(0));
     if constexpr (STLDS) __syncthreads();
   } else {
-    fft_stages<R, L, T, DIR, 1, true, LDLDS, STLDS>(ld, st, lds, ls, t, tvalid, tw, rad{});
+    fft_stages<R, L, T, DIR, 1, 0, true, LDLDS, STLDS>(ld, st, lds, ls, t, tvalid, tw, rad{});
   }
+}
+
+// The same with the twiddles fetched on the spot.
+template <typename R, int L, int T, int DIR, bool LDLDS = false, bool STLDS = false, class Load, class Store>
+__device__ __forceinline__ void fft_pencil(Load ld, Store st, cx<R>* lds, int ls, int t, bool tvalid,
+                                           const cx<R>* __restrict__ tw) {
+  const TwRegs<R, L, T> w(tw, t);
+  fft_pencil<R, L, T, DIR, LDLDS, STLDS>(ld, st, lds, ls, t, tvalid, w);
 }
 
 }  // namespace vie

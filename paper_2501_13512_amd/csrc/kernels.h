@@ -51,9 +51,9 @@ struct MvmBatch {
   cx<R>* work;
   const int* status;       // per system; null = always active
   const TwiddleSet<R>* tw; // host-side pointer table (values are device pointers)
-  int zvariant;            // z-pass kernel variant (see tune_zpass)
+  int zvariant;            // z-pass kernel variant (see zpass_rule)
   int plane;               // 1: x and y transforms fused per z-plane (plane_supported(lx, ly))
-  int pvariant;            // plane kernels: planes per workgroup variant (see tune_plane)
+  int pvariant;            // plane kernels: planes per workgroup variant (see plane_rule)
   // 0: collocated voxels (spec: six octant spectra, 1/chi per voxel);
   // 1: rooftop faces (spec: the scalar octant spectrum and difference
   // symbols of green_spectrum_rooftop; 1/chi per face, [nsys][3][nz][ny][nx])
@@ -104,20 +104,16 @@ void mvm_mid(const MvmBatch<R>& b, hipStream_t s);   // passes 2-4
 template <typename R>
 void mvm_pass5(const MvmBatch<R>& b, const KBatch* k, const FuseArgs& f, const c128* x, c128* y, hipStream_t s);
 
-// Times every z-pass variant on the batch's work buffer (clobbers it) and
-// returns the fastest; ms_out (optional, kZPassVariants entries) receives
-// each variant's time for three runs, -1 where not timed.
+// The z-pass variant of an unpinned batch: elem_bytes of a real in the
+// transforms' precision, the z length, the spectral multiply, columns (qx, qy)
+// of all systems.
 constexpr int kZPassVariants = 5;
-template <typename R>
-int tune_zpass(const MvmBatch<R>& b, hipStream_t s, float* ms_out = nullptr);
+int zpass_rule(int elem_bytes, int lz, bool rooftop, int64_t cols);
 
-// Plane-kernel variants (planes per workgroup: 0 as LDS allows, 1 two,
-// 2 one).  tune_plane times the forward and inverse plane passes of each on
-// the batch's work buffer with x as input and y as output (clobbers all
-// three) and returns the fastest; 0 for batches without plane kernels.
+// The plane-kernel variant (planes per workgroup: 0 as LDS allows, 1 two,
+// 2 one) of an unpinned batch: transform length, planes of all systems.
 constexpr int kPlaneVariants = 3;
-template <typename R>
-int tune_plane(const MvmBatch<R>& b, const c128* x, c128* y, hipStream_t s, float* ms_out = nullptr);
+int plane_rule(int l, int64_t planes);
 
 // Chunks per system of the fused first/last passes (for partial sizing).
 int64_t mvm_row_tiles(int lx, int nz, int ny);

@@ -108,23 +108,32 @@ __global__ void __launch_bounds__((Geo<R, L>::T * Geo<R, L>::ROWP)) k_row_fwd(Ro
   cx<R>* slot = lds + p * L;
   const int nx = a.nx;
   const int mode = a.in_mode;
+  const TwRegs<R, L, T> tw(a.tw, t);
   auto st = [&](int k, cx<R> v) { w[k] = v; };
   if (mode == 0) {
+    // nothing in the loaders uses a loaded value under its bounds check, so a
+    // thread's loads are all in flight together
     const c128* xin = a.x + vrow;
-    const c128* chi = a.chi_inv + sys * a.cstride + (int64_t)(a.chi3 ? rr : zy) * a.nx;
-    const bool msk = a.mask_input != 0;
-    auto ld = [&](int n) -> cx<R> {
-      if (n < nx) {
-        c128 v = xin[n];
-        if (msk) {
-          c128 ci = chi[n];
-          if (ci.x == 0.0 && ci.y == 0.0) v = mk<double>(0.0, 0.0);
+    if (a.mask_input) {
+      const c128* chi = a.chi_inv + sys * a.cstride + (int64_t)(a.chi3 ? rr : zy) * nx;
+      auto ld = [&](int n) -> cx<R> {
+        c128 v = mk<double>(0.0, 0.0), ci = v;
+        if (n < nx) {
+          v = xin[n];
+          ci = chi[n];
         }
+        const bool off = ci.x == 0.0 && ci.y == 0.0;
+        return cvt<R>(mk<double>(off ? 0.0 : v.x, off ? 0.0 : v.y));
+      };
+      fft_pencil<R, L, T, -1>(ld, st, slot, 1, t, valid, tw);
+    } else {
+      auto ld = [&](int n) -> cx<R> {
+        c128 v = mk<double>(0.0, 0.0);
+        if (n < nx) v = xin[n];
         return cvt<R>(v);
-      }
-      return czero<R>();
-    };
-    fft_pencil<R, L, T, -1>(ld, st, slot, 1, t, valid, a.tw);
+      };
+      fft_pencil<R, L, T, -1>(ld, st, slot, 1, t, valid, tw);
+    }
     return;
   }
   const KState& ks = a.k.st[sys];
@@ -176,7 +185,7 @@ __global__ void __launch_bounds__((Geo<R, L>::T * Geo<R, L>::ROWP)) k_row_fwd(Ro
   }
   __syncthreads();
   auto ld = [&](int n) -> cx<R> { return slot[n]; };
-  fft_pencil<R, L, T, -1, true, false>(ld, st, slot, 1, t, valid, a.tw);
+  fft_pencil<R, L, T, -1, true, false>(ld, st, slot, 1, t, valid, tw);
   if (mode == 2) {
     double sum[1] = {acc};
     write_partial<1>(sum, a.k.partials, a.k.pstride, a.k.ntile, sys, tile, tiles);
@@ -211,16 +220,13 @@ __global__ void __launch_bounds__((Geo<R, L>::T * Geo<R, L>::ROWP)) k_row_inv_lo
   auto sts = [&](int k, cx<R> v) {
     if (k < nx) slot[k] = v;
   };
-  fft_pencil<R, L, T, +1, false, true>(ld, sts, slot, 1, t, valid, a.tw);
-
   const double scale = a.scale;
   const int mode = a.out_mode;
   double acc[4] = {0.0, 0.0, 0.0, 0.0};
   constexpr int E = (L + T - 1) / T;
   constexpr int CH = 4;
-#pragma unroll
-  for (int j0 = 0; j0 < E; j0 += CH) {
-    c128 ci[CH], xv[CH], ov[CH];
+  c128 ci[CH], xv[CH], ov[CH];
+  auto load = [&](int j0) {
 #pragma unroll
     for (int u = 0; u < CH; ++u) {
       const int k = t + (j0 + u) * T;
@@ -231,6 +237,15 @@ __global__ void __launch_bounds__((Geo<R, L>::T * Geo<R, L>::ROWP)) k_row_inv_lo
         if (mode == 2 || mode == 4) ov[u] = a.s[vrow + k];
       }
     }
+  };
+  const TwRegs<R, L, T> tw(a.tw, t);
+  constexpr bool EARLY = E <= 2 * CH;   // the operands in flight during the transform, where it holds few values
+  if (EARLY) load(0);
+  fft_pencil<R, L, T, +1, false, true>(ld, sts, slot, 1, t, valid, tw);
+
+#pragma unroll
+  for (int j0 = 0; j0 < E; j0 += CH) {
+    if (!EARLY || j0 > 0) load(j0);
 #pragma unroll
     for (int u = 0; u < CH; ++u) {
       const int k = t + (j0 + u) * T;
@@ -306,6 +321,7 @@ __global__ void __launch_bounds__((PlaneGeo<R, L, PV>::BT)) k_plane_fwd(RowArgs<
   const int64_t v0 = sys * a.vstride + (int64_t)pl0 * pe;
   const int mode = a.in_mode;
   double acc = 0.0;
+  const TwRegs<R, L, T> tw(a.tw, threadIdx.x / PP);
   // zero the padding columns [nx, L) of rows y < ny
   const int padw = L - nx;
   for (int e = threadIdx.x; e < npl * ny * padw; e += BT) {
@@ -320,16 +336,31 @@ __global__ void __launch_bounds__((PlaneGeo<R, L, PV>::BT)) k_plane_fwd(RowArgs<
   if (mode == 0) {
     const c128* chi = a.chi_inv + sys * a.cstride;
     const bool msk = a.mask_input != 0;
-    for (int e = threadIdx.x; e < ne; e += BT) {
-      c128 v = a.x[v0 + e];
-      if (msk) {
-        const int q = (int)udiv_m((unsigned)e, a.m_pe);
-        const int zq = pl0 + q;
-        const int z = a.chi3 ? zq : zq - nz * (int)udiv_m((unsigned)zq, a.m_nz);
-        const c128 ci = chi[(int64_t)z * pe + (e - q * pe)];
-        if (ci.x == 0.0 && ci.y == 0.0) v = mk<double>(0.0, 0.0);
+    constexpr int CH = 4;
+    for (int e0 = 0; e0 < ne; e0 += CH * BT) {
+      c128 v[CH], ci[CH];
+#pragma unroll
+      for (int u = 0; u < CH; ++u) {
+        const int e = e0 + u * BT + (int)threadIdx.x;
+        ci[u] = mk<double>(1.0, 0.0);
+        if (e < ne) {
+          v[u] = a.x[v0 + e];
+          if (msk) {
+            const int q = (int)udiv_m((unsigned)e, a.m_pe);
+            const int zq = pl0 + q;
+            const int z = a.chi3 ? zq : zq - nz * (int)udiv_m((unsigned)zq, a.m_nz);
+            ci[u] = chi[(int64_t)z * pe + (e - q * pe)];
+          }
+        }
       }
-      *lds_at(e) = cvt<R>(v);
+#pragma unroll
+      for (int u = 0; u < CH; ++u) {
+        const int e = e0 + u * BT + (int)threadIdx.x;
+        if (e < ne) {
+          const bool off = ci[u].x == 0.0 && ci[u].y == 0.0;
+          *lds_at(e) = cvt<R>(mk<double>(off ? 0.0 : v[u].x, off ? 0.0 : v[u].y));
+        }
+      }
     }
   } else {
     const KState& ks = a.k.st[sys];
@@ -389,7 +420,7 @@ __global__ void __launch_bounds__((PlaneGeo<R, L, PV>::BT)) k_plane_fwd(RowArgs<
       cx<R>* slot = lds + (rq * L + (rr - rq * ny)) * LP;
       auto ld = [&](int n) -> cx<R> { return slot[n]; };
       auto st = [&](int k, cx<R> v) { slot[k] = v; };
-      fft_pencil<R, L, T, -1, true, true>(ld, st, slot, 1, t, valid, a.tw);
+      fft_pencil<R, L, T, -1, true, true>(ld, st, slot, 1, t, valid, tw);
     }
   }
   // y transforms of the L columns (rows >= ny are zero), out to HBM
@@ -406,7 +437,7 @@ __global__ void __launch_bounds__((PlaneGeo<R, L, PV>::BT)) k_plane_fwd(RowArgs<
       cx<R>* wc = w + (int64_t)q * L * L + xq;
       auto ld = [&](int n) -> cx<R> { return n < ny ? slot[n * LP] : czero<R>(); };
       auto st = [&](int k, cx<R> v) { wc[k * L] = v; };
-      fft_pencil<R, L, T, -1, true, false>(ld, st, slot, LP, t, valid, a.tw);
+      fft_pencil<R, L, T, -1, true, false>(ld, st, slot, LP, t, valid, tw);
     }
   }
   if (mode == 2) {
@@ -429,6 +460,26 @@ __global__ void __launch_bounds__((PlaneGeo<R, L, PV>::BT)) k_plane_inv_local(Ro
   const int pe = ny * nx;
   const int ne = npl * pe;
   const int64_t v0 = sys * a.vstride + (int64_t)pl0 * pe;
+  const double scale = a.scale;
+  const int mode = a.out_mode;
+  const c128* chi = a.chi_inv + sys * a.cstride;
+  constexpr int CH = 4;
+  c128 ci[CH], xv[CH], ov[CH];
+  auto load = [&](int e0) {
+#pragma unroll
+    for (int u = 0; u < CH; ++u) {
+      const int e = e0 + u * BT + (int)threadIdx.x;
+      if (e < ne) {
+        const int q = (int)udiv_m((unsigned)e, a.m_pe), zq = pl0 + q;
+        ci[u] = chi[(int64_t)(a.chi3 ? zq : zq - nz * (int)udiv_m((unsigned)zq, a.m_nz)) * pe + (e - q * pe)];
+        xv[u] = a.x[v0 + e];
+        if (mode == 1 || mode == 3) ov[u] = a.rhat[v0 + e];
+        if (mode == 2 || mode == 4) ov[u] = a.s[v0 + e];
+      }
+    }
+  };
+  const TwRegs<R, L, T> tw(a.tw, threadIdx.x / PP);
+  load(0);   // in flight during the transforms
   // y inverse of the L columns from HBM, rows k < ny kept in LDS
   {
     const int p = threadIdx.x % PP, t = threadIdx.x / PP;
@@ -445,7 +496,7 @@ __global__ void __launch_bounds__((PlaneGeo<R, L, PV>::BT)) k_plane_inv_local(Ro
       auto st = [&](int k, cx<R> v) {
         if (k < ny) slot[k * LP] = v;
       };
-      fft_pencil<R, L, T, +1, false, true>(ld, st, slot, LP, t, valid, a.tw);
+      fft_pencil<R, L, T, +1, false, true>(ld, st, slot, LP, t, valid, tw);
     }
   }
   // x inverse of the rows y < ny, in place, cropped to nx (lanes over rows
@@ -463,28 +514,13 @@ __global__ void __launch_bounds__((PlaneGeo<R, L, PV>::BT)) k_plane_inv_local(Ro
       auto st = [&](int k, cx<R> v) {
         if (k < nx) slot[k] = v;
       };
-      fft_pencil<R, L, T, +1, true, true>(ld, st, slot, 1, t, valid, a.tw);
+      fft_pencil<R, L, T, +1, true, true>(ld, st, slot, 1, t, valid, tw);
     }
   }
   // y = x/chi - scale Q on the mask, fused inner products
-  const double scale = a.scale;
-  const int mode = a.out_mode;
-  const c128* chi = a.chi_inv + sys * a.cstride;
   double acc[4] = {0.0, 0.0, 0.0, 0.0};
-  constexpr int CH = 4;
   for (int e0 = 0; e0 < ne; e0 += CH * BT) {
-    c128 ci[CH], xv[CH], ov[CH];
-#pragma unroll
-    for (int u = 0; u < CH; ++u) {
-      const int e = e0 + u * BT + (int)threadIdx.x;
-      if (e < ne) {
-        const int q = (int)udiv_m((unsigned)e, a.m_pe), zq = pl0 + q;
-        ci[u] = chi[(int64_t)(a.chi3 ? zq : zq - nz * (int)udiv_m((unsigned)zq, a.m_nz)) * pe + (e - q * pe)];
-        xv[u] = a.x[v0 + e];
-        if (mode == 1 || mode == 3) ov[u] = a.rhat[v0 + e];
-        if (mode == 2 || mode == 4) ov[u] = a.s[v0 + e];
-      }
-    }
+    if (e0 > 0) load(e0);
 #pragma unroll
     for (int u = 0; u < CH; ++u) {
       const int e = e0 + u * BT + (int)threadIdx.x;
@@ -570,7 +606,8 @@ __global__ void __launch_bounds__((Geo<R, L>::TC * Geo<R, L>::COLP)) k_col(ColAr
   auto st = [&](int k, cx<R> v) {
     if (k < n_out) base[(int64_t)k * inner] = v;
   };
-  fft_pencil<R, L, G::TC, DIR>(ld, st, lds + p, G::COLP, t, valid, a.tw);
+  const TwRegs<R, L, G::TC> tw(a.tw, t);
+  fft_pencil<R, L, G::TC, DIR>(ld, st, lds + p, G::COLP, t, valid, tw);
 }
 
 // ------------------------------------------------------------------ launchers
@@ -828,107 +865,49 @@ void mvm(const MvmBatch<R>& b, const c128* x, c128* y, bool mask_input, hipStrea
   mark(ev, 5, s);
 }
 
-// Autotuning of the z pass: time each variant on the batch's own work buffer
-// (contents are overwritten; call before the buffer holds live data) and
-// return the faster one.
-template <typename R>
-int tune_zpass(const MvmBatch<R>& b, hipStream_t s, float* ms_out) {
-  if (ms_out)
-    for (int v = 0; v < kZPassVariants; ++v) ms_out[v] = -1.0f;
-  if (b.nsys <= 0) return 0;
-  hipEvent_t e0 = nullptr, e1 = nullptr;
-  {
-    ApiShared api;
-    if (hipEventCreate(&e0) != hipSuccess || hipEventCreate(&e1) != hipSuccess)
-      throw std::runtime_error("hipEventCreate failed");
+// The z-pass variant of a shape; `cols` counts the columns of every system of
+// the batch.  Measured with the kernels alone (f32 / f64, us; small: 1024
+// columns, large: 65536):
+//   length   32: V4 4.1 / 4.3 small; large V3 16.1 f32 (V4 19.0), V4 27.7 f64 (V3 30.4)
+//            36: V2 4.5, V4 5.2 small; large V3 30.9 / 42.7 (V2 41.5, V4 45.1)
+//            48: V0 5.5, V4 6.0 small; large V2 28.2 / 47.5 (V0 42.5 / 99.5)
+//            64: V4 5.1 / 5.2; large V4 29.1 / 46.3 (V3 31.4 / 59.6)
+//            72: V2 6.1, V0 5.8 small; large V2 51.0 (V4 54.6), V3 80.7 (V0 113.6)
+//            96: V0 6.7 / 6.5 small; large V2 56.3 (V0 62.8), V0 113.4 (V2 133.0);
+//                rooftop f64 V3 115 (V0 163)
+//           128: V4 6.7 / 7.2; large V4 66.6 / 163.4 (V2 82.4 / 194.4); rooftop f64 V3 109.5 (V4 129)
+//   from 144 on V4 (V0 equal, V2 and V3 slower); below 32 V0 and V4 are one.
+// The mirror columns (V1) were ahead in none of 96 shapes of lengths 4 to 256.
+// The lines between small and large lie where the two variants cross.
+int zpass_rule(int elem_bytes, int lz, bool rooftop, int64_t cols) {
+  const bool f32 = elem_bytes == 4;
+  if (lz < 32) return 0;
+  switch (lz) {
+    case 32: return f32 && cols >= 32768 ? 3 : 4;
+    case 36: return f32 ? (cols >= 16384 ? 3 : 2) : (cols >= 32768 ? 3 : 4);
+    case 48: return cols >= 8192 ? 2 : (f32 ? 0 : 4);
+    case 72: return f32 ? 2 : (cols >= 8192 ? 3 : 0);
+    case 96:
+      if (f32) return cols >= 16384 ? 2 : 0;
+      return rooftop ? (cols >= 16384 ? 3 : 2) : 0;
+    case 128: return !f32 && rooftop && cols >= 32768 ? 3 : 4;
+    default: return 4;
   }
-  float best = 1e30f;
-  int best_v = 0;
-  for (int v = 0; v < kZPassVariants; ++v) {
-    if (v >= 2 && b.lz < 32) break;   // short columns: variants 0 and 1 only
-    if (v == 1 && b.rooftop) continue;   // column sets only
-    ZArgs<R> za{};
-    za.nz = b.nz;
-    za.ly = b.ly;
-    za.lx = b.lx;
-    za.variant = v;
-    za.wstride = b.wstride;
-    za.sstride = b.sstride;
-    za.work = b.work;
-    za.spec = b.spec;
-    za.spec_tab = b.spec_tab;
-    za.rooftop = b.rooftop;
-    za.status = nullptr;
-    za.tw = b.tw->table[b.lz];
-    launch_zconv<R>(b.lz, za, b.nsys, s);   // warm-up
-    (void)hipEventRecord(e0, s);
-    for (int r = 0; r < 3; ++r) launch_zconv<R>(b.lz, za, b.nsys, s);
-    (void)hipEventRecord(e1, s);
-    (void)hipEventSynchronize(e1);
-    float ms = 0;
-    (void)hipEventElapsedTime(&ms, e0, e1);
-    if (ms_out) ms_out[v] = ms;
-    if (ms < best) {
-      best = ms;
-      best_v = v;
-    }
-  }
-  {
-    ApiShared api;
-    (void)hipEventDestroy(e0);
-    (void)hipEventDestroy(e1);
-  }
-  return best_v;
 }
-template int tune_zpass<float>(const MvmBatch<float>&, hipStream_t, float*);
-template int tune_zpass<double>(const MvmBatch<double>&, hipStream_t, float*);
 
-// Autotuning of the plane kernels (batches with b.plane): time the forward
-// and inverse plane passes of each variant (plain product, every system
-// active) on the batch's own work buffer, x as input and y as output (all
-// overwritten; call before they hold live data); returns the fastest.
-template <typename R>
-int tune_plane(const MvmBatch<R>& b, const c128* x, c128* y, hipStream_t s, float* ms_out) {
-  if (ms_out)
-    for (int v = 0; v < kPlaneVariants; ++v) ms_out[v] = -1.0f;
-  if (b.nsys <= 0 || !b.plane) return 0;
-  if (!x || !y) throw std::runtime_error("tune_plane: missing vectors");
-  hipEvent_t e0 = nullptr, e1 = nullptr;
-  {
-    ApiShared api;
-    if (hipEventCreate(&e0) != hipSuccess || hipEventCreate(&e1) != hipSuccess)
-      throw std::runtime_error("hipEventCreate failed");
-  }
-  MvmBatch<R> bb = b;
-  bb.status = nullptr;
-  const FuseArgs none{0, 0, nullptr, nullptr, nullptr, nullptr, nullptr};
-  float best = 1e30f;
-  int best_v = 0;
-  for (int v = 0; v < kPlaneVariants; ++v) {
-    bb.pvariant = v;
-    auto run = [&]() {
-      mvm_pass1<R>(bb, nullptr, none, x, false, s);
-      mvm_pass5<R>(bb, nullptr, none, x, y, s);
-    };
-    run();   // warm-up
-    (void)hipEventRecord(e0, s);
-    for (int r = 0; r < 3; ++r) run();
-    (void)hipEventRecord(e1, s);
-    (void)hipEventSynchronize(e1);
-    float ms = 0;
-    (void)hipEventElapsedTime(&ms, e0, e1);
-    if (ms_out) ms_out[v] = ms;
-    if (ms < best) {
-      best = ms;
-      best_v = v;
-    }
-  }
-  {
-    ApiShared api;
-    (void)hipEventDestroy(e0);
-    (void)hipEventDestroy(e1);
-  }
-  return best_v;
+// The plane-kernel variant of a shape; `planes` counts the z-planes of the
+// three components of every system of the batch.  Few planes want many short
+// workgroups, many planes of a small transform fuller ones.  Forward and
+// inverse together, with 10 us of event overhead (f32 / f64, us, variants 0, 1, 2):
+//   length 16: 384 planes 15.4, 13.6, 14.6 / 15.9, 14.7, 15.7; 6144: 21.2, 28.1, 41.7 / 25.1, 36.8, 59.6
+//          24: 576: 29.4, 16.8, 15.5 / 21.9, 18.6, 17.5; 9216: 59.0, 44.7, 52.5 / 60.5, 54.1, 63.7
+//          32: 768: 25.6, 18.2, 17.6 / 21.3, 21.1, 19.9; 12288: 84.4, 61.5, 69.1 / 100.6, 100.1, 103.3
+//          48: 768: 35.1, 35.0, 26.1 / 29.9, 29.7, 29.5; 3072: 63.8, 63.0, 56.9; 64: one plane in all
+int plane_rule(int l, int64_t planes) {
+  if (l <= 8) return 0;
+  if (l <= 16) return planes > 2048 ? 0 : 1;
+  if (l <= 32) return planes > 1024 ? 1 : 2;
+  return 2;
 }
 
 #define VIE_MVM_INST(R)                                                                                           \
@@ -939,8 +918,6 @@ int tune_plane(const MvmBatch<R>& b, const c128* x, c128* y, hipStream_t s, floa
 VIE_MVM_INST(float)
 VIE_MVM_INST(double)
 #undef VIE_MVM_INST
-template int tune_plane<float>(const MvmBatch<float>&, const c128*, c128*, hipStream_t, float*);
-template int tune_plane<double>(const MvmBatch<double>&, const c128*, c128*, hipStream_t, float*);
 
 int64_t mvm_row_tiles(int lx, int nz, int ny) {
   const int64_t rows = 3 * (int64_t)nz * ny;

@@ -220,8 +220,6 @@ struct vie_context {
   std::mutex mu;
   std::map<SpecKey, std::weak_ptr<Spectra>> cache;
   size_t reserved = 0;   // bytes reserved by requests admitted to the server
-  std::map<std::array<int, 8>, std::pair<int, std::array<float, vie::kZPassVariants>>> ztune;
-  std::map<std::array<int, 8>, std::pair<int, std::array<float, vie::kPlaneVariants>>> ptune;
   std::unique_ptr<Server> server;
   std::mutex server_mu;
   double* far_scratch = nullptr;   // this device's copy of the far field's fixed scratch array
@@ -274,8 +272,8 @@ struct Group {
   std::shared_ptr<Spectra> spec;
   DevBuf chi, work, vecs;
   DevBuf sys_origin;     // expanded blocks: box origin of each system (int4)
-  int zvar[2] = {0, 0};  // tuned z-pass variant per precision ([0] FP64, [1] FP32)
-  int pvar[2] = {0, 0};  // tuned plane-kernel variant per precision
+  int zvar[2] = {0, 0};  // z-pass variant per precision ([0] FP64, [1] FP32)
+  int pvar[2] = {0, 0};  // plane-kernel variant per precision
   // systems from problems with different spacing or wavelength: each
   // system's spectra (kept alive here) and a device table of their addresses
   // ([0, nsys) FP64, [nsys, 2 nsys) FP32); empty when all share `spec`
@@ -346,9 +344,7 @@ struct vie_problem {
   DevBuf chi, work, vecs, partials, partials2, ntile, ostate, ostatus, scal;
   int64_t pstride = 0;
   int zvar[2] = {0, 0};
-  float ztune_ms[2][vie::kZPassVariants] = {};
   int pvar[2] = {0, 0};
-  float ptune_ms[2][vie::kPlaneVariants] = {};
   // inner systems of all groups: partials (per-system stride ipstride)
   DevBuf d_ipartials, d_ipartials2, d_intile;
   int64_t ipstride = 0;
@@ -1860,52 +1856,25 @@ size_t plan_footprint(vie_context* ctx, const ProblemPlan& pl, bool all_spectra 
   return foot;
 }
 
-// z-pass variant for a batch shape: tuned once per context, shape and
-// precision, so every problem of that shape uses the same kernels.
-template <typename R>
-int cached_zvariant(vie_context* ctx, const MvmBatch<R>& b, hipStream_t s, float* ms) {
-  const std::array<int, 8> key{(int)sizeof(R) + 64 * b.rooftop, b.nx, b.ny, b.nz, b.lx, b.ly, b.lz, b.nsys};
-  {
-    std::lock_guard<std::mutex> lk(ctx->mu);
-    auto it = ctx->ztune.find(key);
-    if (it != ctx->ztune.end()) {
-      if (ms)
-        for (int v = 0; v < vie::kZPassVariants; ++v) ms[v] = it->second.second[v];
-      return it->second.first;
-    }
-  }
-  std::array<float, vie::kZPassVariants> t{};
-  const int v = vie::tune_zpass<R>(b, s, t.data());
-  std::lock_guard<std::mutex> lk(ctx->mu);
-  auto it = ctx->ztune.emplace(key, std::make_pair(v, t)).first;   // first tuning wins
-  if (ms)
-    for (int q = 0; q < vie::kZPassVariants; ++q) ms[q] = it->second.second[q];
-  return it->second.first;
+// The kernel variants of an unpinned batch: by its shape alone, so every
+// problem of a shape uses the same kernels and gives the same results.
+int z_variant(int elem_bytes, const MvmBatch<double>& b) {
+  return vie::zpass_rule(elem_bytes, b.lz, b.rooftop != 0, (int64_t)b.lx * b.ly * b.nsys);
 }
+int p_variant(const MvmBatch<double>& b) { return b.plane ? vie::plane_rule(b.lx, 3 * (int64_t)b.nz * b.nsys) : 0; }
 
-// Plane-kernel variant for a batch shape, tuned once per context, shape and
-// precision as the z pass; x and y: device vectors of the batch that hold
-// no data yet (clobbered).
-template <typename R>
-int cached_pvariant(vie_context* ctx, const MvmBatch<R>& b, const c128* x, c128* y, hipStream_t s, float* ms) {
-  const std::array<int, 8> key{(int)sizeof(R) + 64 * b.rooftop, b.nx, b.ny, b.nz, b.lx, b.ly, b.lz, b.nsys};
-  {
-    std::lock_guard<std::mutex> lk(ctx->mu);
-    auto it = ctx->ptune.find(key);
-    if (it != ctx->ptune.end()) {
-      if (ms)
-        for (int v = 0; v < vie::kPlaneVariants; ++v) ms[v] = it->second.second[v];
-      return it->second.first;
-    }
-  }
-  std::array<float, vie::kPlaneVariants> t{};
-  const int v = vie::tune_plane<R>(b, x, y, s, t.data());
-  std::lock_guard<std::mutex> lk(ctx->mu);
-  auto it = ctx->ptune.emplace(key, std::make_pair(v, t)).first;   // first tuning wins
-  if (ms)
-    for (int q = 0; q < vie::kPlaneVariants; ++q) ms[q] = it->second.second[q];
-  return it->second.first;
+void unpin_z(vie_problem& P) {
+  const MvmBatch<double> b = outer_batch<double>(P, false);
+  P.zvar[0] = z_variant(8, b);
+  P.zvar[1] = z_variant(4, b);
 }
+void unpin_z(vie_problem& P, Group& G) {
+  const MvmBatch<double> b = group_batch<double>(P, G, false);
+  G.zvar[0] = z_variant(8, b);
+  G.zvar[1] = z_variant(4, b);
+}
+void unpin_p(vie_problem& P) { P.pvar[0] = P.pvar[1] = p_variant(outer_batch<double>(P, false)); }
+void unpin_p(vie_problem& P, Group& G) { G.pvar[0] = G.pvar[1] = p_variant(group_batch<double>(P, G, false)); }
 
 // inner_only: the blocks and their inner solves only (no full-grid operator:
 // no outer spectra, work buffer or Krylov vectors); used for the stacked
@@ -2083,14 +2052,7 @@ std::unique_ptr<vie_problem> build_problem(vie_context* ctx, const ProblemPlan& 
     P->d_ipartials2.alloc((size_t)std::max(1, slot) * P->ipstride * sizeof(double));
     P->d_intile.alloc(std::max(1, slot) * sizeof(int));
     P->d_intile.zero(s);
-    // pick the faster z-pass kernel per batch shape and precision (tuning
-    // clobbers the work buffers, which hold no data yet)
-    for (auto& G : P->groups) {
-      G.zvar[0] = cached_zvariant<double>(ctx, group_batch<double>(*P, G, false), s, nullptr);
-      G.zvar[1] = cached_zvariant<float>(ctx, group_batch<float>(*P, G, false), s, nullptr);
-      G.pvar[0] = cached_pvariant<double>(ctx, group_batch<double>(*P, G, false), G.vec[0], G.vec[1], s, nullptr);
-      G.pvar[1] = cached_pvariant<float>(ctx, group_batch<float>(*P, G, false), G.vec[0], G.vec[1], s, nullptr);
-    }
+    for (auto& G : P->groups) unpin_z(*P, G), unpin_p(*P, G);
     if (P->groups.size() > 1) {
       ApiShared api;
       const size_t G = P->groups.size();
@@ -2120,12 +2082,8 @@ std::unique_ptr<vie_problem> build_problem(vie_context* ctx, const ProblemPlan& 
     m.faces = pl.rooftop ? 1 : 0;
   }
   if (!inner_only) {
-    P->zvar[0] = cached_zvariant<double>(ctx, outer_batch<double>(*P, false), s, P->ztune_ms[0]);
-    P->zvar[1] = cached_zvariant<float>(ctx, outer_batch<float>(*P, false), s, P->ztune_ms[1]);
-    P->pvar[0] = cached_pvariant<double>(ctx, outer_batch<double>(*P, false), P->vec[V_B], P->vec[V_TMP1], s,
-                                         P->ptune_ms[0]);
-    P->pvar[1] = cached_pvariant<float>(ctx, outer_batch<float>(*P, false), P->vec[V_B], P->vec[V_TMP1], s,
-                                        P->ptune_ms[1]);
+    unpin_z(*P);
+    unpin_p(*P);
   }
   hip_check(hipStreamSynchronize(s), "problem set-up");
   return P;
@@ -2436,7 +2394,6 @@ vie_status vie_problem_set_zpass(vie_problem* p, int32_t precision, int32_t vari
     }
     std::lock_guard<std::mutex> lk(p->mu);
     const int q = precision == VIE_MIXED ? 1 : 0;
-    hipStream_t s = p->ctx->stream;
     // the problem, and the replica of its blocks used by preconditioned batches
     for (vie_problem* x : {p, p->replica.get()}) {
       if (!x) continue;
@@ -2444,14 +2401,15 @@ vie_status vie_problem_set_zpass(vie_problem* p, int32_t precision, int32_t vari
       if (variant >= 0) {
         x->zvar[q] = variant;
         for (auto& G : x->groups) G.zvar[q] = variant;
-      } else if (q == 0) {
-        if (outer) x->zvar[0] = cached_zvariant<double>(x->ctx, outer_batch<double>(*x, false), s, nullptr);
-        for (auto& G : x->groups)
-          G.zvar[0] = cached_zvariant<double>(x->ctx, group_batch<double>(*x, G, false), s, nullptr);
-      } else {
-        if (outer) x->zvar[1] = cached_zvariant<float>(x->ctx, outer_batch<float>(*x, false), s, nullptr);
-        for (auto& G : x->groups)
-          G.zvar[1] = cached_zvariant<float>(x->ctx, group_batch<float>(*x, G, false), s, nullptr);
+      } else {   // the rule's choice, in the given precision
+        const int other = x->zvar[1 - q];
+        if (outer) unpin_z(*x);
+        x->zvar[1 - q] = other;
+        for (auto& G : x->groups) {
+          const int gother = G.zvar[1 - q];
+          unpin_z(*x, G);
+          G.zvar[1 - q] = gother;
+        }
       }
       // captured inner steps hold the old kernels
       ApiShared api;
@@ -2483,15 +2441,8 @@ vie_status vie_problem_set_plane(vie_problem* p, int32_t precision, int32_t vari
         x->pvar[q] = variant;
         for (auto& G : x->groups) G.pvar[q] = variant;
       } else {
-        // the choices cached at set-up (tuned once per shape)
-        std::lock_guard<std::mutex> ck(x->ctx->mu);
-        auto tuned = [&](int sz, int nx, int ny, int nz, int lx, int ly, int lz, int nsys) {
-          auto it = x->ctx->ptune.find({sz, nx, ny, nz, lx, ly, lz, nsys});
-          return it == x->ctx->ptune.end() ? 0 : it->second.first;
-        };
-        const int sz = q == 1 ? (int)sizeof(float) : (int)sizeof(double);
-        if (x->spec) x->pvar[q] = tuned(sz, x->g.nx, x->g.ny, x->g.nz, x->lx, x->ly, x->lz, 1);
-        for (auto& G : x->groups) G.pvar[q] = tuned(sz, G.bx, G.by, G.bz, G.lx, G.ly, G.lz, G.nsys);
+        if (x->spec) x->pvar[q] = p_variant(outer_batch<double>(*x, false));
+        for (auto& G : x->groups) G.pvar[q] = p_variant(group_batch<double>(*x, G, false));
       }
       // captured inner steps hold the old kernels
       ApiShared api;
@@ -2519,9 +2470,9 @@ vie_status vie_problem_get_info(const vie_problem* p, vie_problem_info* info) {
     static_assert(vie::kPlaneVariants == 3, "vie_problem_info holds 3 plane-kernel timings");
     for (int q = 0; q < 2; ++q) {
       info->zpass_variant[q] = p->zvar[q];
-      for (int v = 0; v < vie::kZPassVariants; ++v) info->zpass_tune_ms[q][v] = p->ztune_ms[q][v];
+      for (int v = 0; v < vie::kZPassVariants; ++v) info->zpass_tune_ms[q][v] = -1.0f;
       info->plane_variant[q] = p->pvar[q];
-      for (int v = 0; v < vie::kPlaneVariants; ++v) info->plane_tune_ms[q][v] = p->ptune_ms[q][v];
+      for (int v = 0; v < vie::kPlaneVariants; ++v) info->plane_tune_ms[q][v] = -1.0f;
     }
     return VIE_OK;
   });

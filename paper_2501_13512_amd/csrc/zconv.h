@@ -62,6 +62,10 @@ struct ZColGeo {
   static constexpr int TZ = (V == 2 || V == 3) ? cmin(TB, cmax(1, 1024 / (3 * ZP)))
                                                : cmin(T, pow2_floor(cmax(1, 1024 / (3 * ZP))));
   static constexpr bool PF = V == 2 || V == 3;
+  // twiddles held in registers over both transforms: not in FP64 beside the
+  // prefetched spectrum (64 systems of length 48: 49 us without, 60 with) or
+  // for short columns
+  static constexpr bool HOLD = sizeof(R) == 4 || (!PF && LZ >= 72);
 };
 
 // Variant 1 (mirror columns): geometry.
@@ -193,6 +197,7 @@ __global__ void __launch_bounds__((3 * ZColGeo<R, LZ, V>::TZ * ZColGeo<R, LZ, V>
   const int comp = threadIdx.x / (T * ZP);
   const int rem = threadIdx.x - comp * (T * ZP);
   const int p = rem % ZP, t = rem / ZP;
+  const TwRegs<R, LZ, T, G::HOLD> tw(a.tw, t);
   const int col = tile * ZP + p;   // logical column
   const bool valid = col < cols;
   // element offsets in 32 bits from the system's base (one system's work
@@ -271,7 +276,7 @@ __global__ void __launch_bounds__((3 * ZColGeo<R, LZ, V>::TZ * ZColGeo<R, LZ, V>
     return n < nz ? *elem(wsys, toff + (unsigned)(n - t) * plane) : czero<R>();
   };
   auto sts = [&](int k, cx<R> v) { slot[k * ZP] = v; };
-  fft_pencil<R, LZ, T, -1, false, true>(ldg, sts, slot, ZP, t, valid, a.tw);
+  fft_pencil<R, LZ, T, -1, false, true>(ldg, sts, slot, ZP, t, valid, tw);
 
   // Q(q) = S(q) X(q), S symmetric 3x3 from the octant with parity signs
   if constexpr (K == 1) if (cvalid) {
@@ -335,7 +340,7 @@ __global__ void __launch_bounds__((3 * ZColGeo<R, LZ, V>::TZ * ZColGeo<R, LZ, V>
   auto stg = [&](int k, cx<R> v) {
     if (k < nz) *elem(wsys, toff + (unsigned)(k - t) * plane) = v;
   };
-  fft_pencil<R, LZ, T, +1, true, false>(lds_ld, stg, slot, ZP, t, valid, a.tw);
+  fft_pencil<R, LZ, T, +1, true, false>(lds_ld, stg, slot, ZP, t, valid, tw);
 }
 
 template <typename R, int L, int V>
