@@ -23,9 +23,29 @@ __host__ __device__ __forceinline__ cx<R> rot_q(cx<R> a) {  // a * exp(DIR * i p
   return DIR < 0 ? mul_mi(a) : mul_i(a);
 }
 
-template <int RAD, int DIR, typename R>
+__host__ __device__ __forceinline__ float fma1(float a, float b, float c) { return __builtin_fmaf(a, b, c); }
+__host__ __device__ __forceinline__ double fma1(double a, double b, double c) { return __builtin_fma(a, b, c); }
+// HALF: the inputs v[RAD/2 ...] are zero (their values are not read), which
+// spares the first of the log2(RAD) levels of additions.
+// SPLIT: the products of the last level are rounded before they are added, so
+// an output's value does not depend on whether its partner (the same product
+// with the other sign) is formed as well.
+template <bool SPLIT, typename R>
+__host__ __device__ __forceinline__ R prod(R a, R b) {
+  if constexpr (SPLIT) {
+#pragma clang fp contract(off)
+    return a * b;
+  } else {
+    return a * b;
+  }
+}
+template <int RAD, int DIR, bool HALF = false, bool SPLIT = false, typename R>
 __host__ __device__ __forceinline__ void dft(cx<R>* v) {
+  static_assert(!HALF || RAD % 2 == 0, "an odd radix has no half");
+  static_assert(!SPLIT || RAD <= 8, "the last level of radix 16 is not split");
   if constexpr (RAD == 1) {
+  } else if constexpr (RAD == 2 && HALF) {
+    v[1] = v[0];
   } else if constexpr (RAD == 2) {
     cx<R> a = v[0], b = v[1];
     v[0] = a + b;
@@ -35,10 +55,16 @@ __host__ __device__ __forceinline__ void dft(cx<R>* v) {
     const R s = DIR < 0 ? R(-0.86602540378443864676) : R(0.86602540378443864676);
     cx<R> t1 = v[1] + v[2], t2 = v[1] - v[2];
     cx<R> m = v[0] + c * t1;
-    cx<R> j = mk<R>(-s * t2.y, s * t2.x);  // i * s * t2
+    cx<R> j = mk<R>(prod<SPLIT>(-s, t2.y), prod<SPLIT>(s, t2.x));  // i * s * t2
     v[0] = v[0] + t1;
     v[1] = m + j;
     v[2] = m - j;
+  } else if constexpr (RAD == 4 && HALF) {
+    const cx<R> e = v[0], o0 = v[1], o1 = rot_q<DIR>(v[1]);
+    v[0] = e + o0;
+    v[2] = e - o0;
+    v[1] = e + o1;
+    v[3] = e - o1;
   } else if constexpr (RAD == 4) {
     cx<R> e0 = v[0] + v[2], e1 = v[0] - v[2];
     cx<R> o0 = v[1] + v[3], o1 = rot_q<DIR>(v[1] - v[3]);
@@ -47,15 +73,20 @@ __host__ __device__ __forceinline__ void dft(cx<R>* v) {
     v[1] = e1 + o1;
     v[3] = e1 - o1;
   } else if constexpr (RAD == 8) {
-    cx<R> e[4] = {v[0], v[2], v[4], v[6]};
-    cx<R> o[4] = {v[1], v[3], v[5], v[7]};
-    dft<4, DIR>(e);
-    dft<4, DIR>(o);
+    constexpr int IN = HALF ? 2 : 4;
+    cx<R> e[4], o[4];
+#pragma unroll
+    for (int i = 0; i < IN; ++i) {
+      e[i] = v[2 * i];
+      o[i] = v[2 * i + 1];
+    }
+    dft<4, DIR, HALF>(e);
+    dft<4, DIR, HALF>(o);
     const R h = R(0.70710678118654752440);
     const R sg = DIR < 0 ? R(-1) : R(1);
-    cx<R> t1 = mk<R>(h * (o[1].x - sg * o[1].y), h * (o[1].y + sg * o[1].x));       // w8^1
-    cx<R> t2 = rot_q<DIR>(o[2]);                                                    // w8^2
-    cx<R> t3 = mk<R>(h * (-o[3].x - sg * o[3].y), h * (-o[3].y + sg * o[3].x));     // w8^3
+    cx<R> t1 = mk<R>(prod<SPLIT>(h, o[1].x - sg * o[1].y), prod<SPLIT>(h, o[1].y + sg * o[1].x));     // w8^1
+    cx<R> t2 = rot_q<DIR>(o[2]);                                                                      // w8^2
+    cx<R> t3 = mk<R>(prod<SPLIT>(h, -o[3].x - sg * o[3].y), prod<SPLIT>(h, -o[3].y + sg * o[3].x));   // w8^3
     v[0] = e[0] + o[0];
     v[4] = e[0] - o[0];
     v[1] = e[1] + t1;
@@ -65,14 +96,15 @@ __host__ __device__ __forceinline__ void dft(cx<R>* v) {
     v[3] = e[3] + t3;
     v[7] = e[3] - t3;
   } else if constexpr (RAD == 16) {
+    constexpr int IN = HALF ? 4 : 8;
     cx<R> e[8], o[8];
 #pragma unroll
-    for (int i = 0; i < 8; ++i) {
+    for (int i = 0; i < IN; ++i) {
       e[i] = v[2 * i];
       o[i] = v[2 * i + 1];
     }
-    dft<8, DIR>(e);
-    dft<8, DIR>(o);
+    dft<8, DIR, HALF>(e);
+    dft<8, DIR, HALF>(o);
     const R c1 = R(0.92387953251128675613), s1 = R(0.38268343236508977173);
     const R h = R(0.70710678118654752440);
     const R sg = DIR < 0 ? R(-1) : R(1);
@@ -209,13 +241,19 @@ struct TwRegs {
 // v w (forward) or v conj(w), with its fused operations spelled out: kernels
 // that hold their twiddles and kernels that load them agree bit for bit, which
 // they need not when the compiler chooses what to contract.
-__device__ __forceinline__ float fma1(float a, float b, float c) { return __builtin_fmaf(a, b, c); }
-__device__ __forceinline__ double fma1(double a, double b, double c) { return __builtin_fma(a, b, c); }
 template <int DIR, typename R>
 __device__ __forceinline__ cx<R> twiddled(cx<R> v, cx<R> w) {
   const R p = v.y * w.y, q = v.x * w.y;
   return DIR < 0 ? mk<R>(fma1(v.x, w.x, -p), fma1(v.y, w.x, q)) : mk<R>(fma1(v.x, w.x, p), fma1(v.y, w.x, -q));
 }
+
+// What half of an even-length pencil is known at compile time: every axis of
+// a product is padded to at least twice its voxels less one, so a forward
+// transform's upper half of inputs is zero and an inverse's upper half of
+// outputs is dropped.
+enum Pad { PAD_NONE = 0, PAD_IN = 1, PAD_OUT = 2 };
+// elements of a padded pencil that can be voxels
+__host__ __device__ constexpr int half_padded(int l) { return l % 2 == 0 ? l / 2 : (l + 1) / 2; }
 
 // One stage.  Threads t < T of a pencil cooperate; `lds` points at element 0
 // of this pencil's LDS slot and consecutive elements are `ls` apart.  All
@@ -223,21 +261,25 @@ __device__ __forceinline__ cx<R> twiddled(cx<R> v, cx<R> w) {
 // LDLDS: the loader reads this pencil's LDS slot; STLDS: the storer writes
 // it.  Then the first (last) stage separates its reads from its writes by a
 // barrier, since the transform runs in place in the slot.
-template <typename R, int L, int T, int DIR, int RAD, int P, int AT, bool FIRST, bool LAST, bool LDLDS, bool STLDS,
-          class Load, class Store, bool HOLD>
+template <typename R, int L, int T, int DIR, int PAD, int RAD, int P, int AT, bool FIRST, bool LAST, bool LDLDS,
+          bool STLDS, class Load, class Store, bool HOLD>
 __device__ __forceinline__ void fft_stage(Load& ld, Store& st, cx<R>* lds, int ls, int t, bool tvalid,
                                           const TwRegs<R, L, T, HOLD>& tw) {
   constexpr int NB = L / RAD;
   constexpr int NPT = (NB + T - 1) / T;
   constexpr bool READS_SLOT = !FIRST || LDLDS;
   constexpr bool WRITES_SLOT = !LAST || STLDS;
+  constexpr bool HIN = FIRST && PAD == PAD_IN && L % 2 == 0 && RAD % 2 == 0;
+  // the last stage's outputs b + m P, b < P: none of m from here on is kept
+  // (radix 16 forms them all: it would spare a ninth of its additions)
+  constexpr int MOUT = LAST && PAD == PAD_OUT && L % 2 == 0 && RAD <= 8 ? (RAD + 1) / 2 : RAD;
   cx<R> v[NPT][RAD];
 #pragma unroll
   for (int q = 0; q < NPT; ++q) {
     const int b = t + q * T;
     if (tvalid && (NB % T == 0 || b < NB)) {
 #pragma unroll
-      for (int m = 0; m < RAD; ++m) {
+      for (int m = 0; m < (HIN ? RAD / 2 : RAD); ++m) {
         const int idx = b + m * NB;
         if constexpr (FIRST)
           v[q][m] = ld(idx);
@@ -256,10 +298,10 @@ __device__ __forceinline__ void fft_stage(Load& ld, Store& st, cx<R>* lds, int l
 #pragma unroll
         for (int m = 1; m < RAD; ++m) v[q][m] = twiddled<DIR>(v[q][m], tw.template at<AT, RAD, P>(q, m, k));
       }
-      dft<RAD, DIR>(v[q]);
+      dft<RAD, DIR, HIN, MOUT != RAD>(v[q]);
       const int j = (b - k) * RAD + k;
 #pragma unroll
-      for (int m = 0; m < RAD; ++m) {
+      for (int m = 0; m < MOUT; ++m) {
         if constexpr (LAST)
           st(j + m * P, v[q][m]);
         else
@@ -270,23 +312,24 @@ __device__ __forceinline__ void fft_stage(Load& ld, Store& st, cx<R>* lds, int l
   if constexpr (WRITES_SLOT) __syncthreads();
 }
 
-template <typename R, int L, int T, int DIR, int P, int AT, bool FIRST, bool LDLDS, bool STLDS, class Load, class Store,
-          bool HOLD, int RAD, int... Rest>
+template <typename R, int L, int T, int DIR, int PAD, int P, int AT, bool FIRST, bool LDLDS, bool STLDS, class Load,
+          class Store, bool HOLD, int RAD, int... Rest>
 __device__ __forceinline__ void fft_stages(Load& ld, Store& st, cx<R>* lds, int ls, int t, bool tvalid,
                                            const TwRegs<R, L, T, HOLD>& tw, Radices<RAD, Rest...>) {
   constexpr bool LAST = sizeof...(Rest) == 0;
   constexpr int NEXT = AT + (P > 1 ? (RAD - 1) * ((L / RAD + T - 1) / T) : 0);
-  fft_stage<R, L, T, DIR, RAD, P, AT, FIRST, LAST, LDLDS, STLDS>(ld, st, lds, ls, t, tvalid, tw);
+  fft_stage<R, L, T, DIR, PAD, RAD, P, AT, FIRST, LAST, LDLDS, STLDS>(ld, st, lds, ls, t, tvalid, tw);
   if constexpr (!LAST)
-    fft_stages<R, L, T, DIR, P * RAD, NEXT, false, LDLDS, STLDS>(ld, st, lds, ls, t, tvalid, tw, Radices<Rest...>{});
+    fft_stages<R, L, T, DIR, PAD, P * RAD, NEXT, false, LDLDS, STLDS>(ld, st, lds, ls, t, tvalid, tw, Radices<Rest...>{});
 }
 
 // Transform one pencil of length L: x_n = ld(n) (n < L) -> st(k, X_k).
 // Threads t in [0, T) of the pencil take part; tvalid = false threads still
 // hit the barriers but touch no data.  The pencil's LDS slot is the exchange
-// buffer between stages; see fft_stage for LDLDS / STLDS.
-template <typename R, int L, int T, int DIR, bool LDLDS = false, bool STLDS = false, class Load, class Store,
-          bool HOLD>
+// buffer between stages; see fft_stage for LDLDS / STLDS.  With PAD_IN (even
+// L) ld is not asked for n >= L/2; with PAD_OUT st may not be given k >= L/2.
+template <typename R, int L, int T, int DIR, bool LDLDS = false, bool STLDS = false, int PAD = PAD_NONE, class Load,
+          class Store, bool HOLD>
 __device__ __forceinline__ void fft_pencil(Load ld, Store st, cx<R>* lds, int ls, int t, bool tvalid,
                                            const TwRegs<R, L, T, HOLD>& tw) {
   using rad = typename Plan<L>::type;
@@ -294,16 +337,17 @@ __device__ __forceinline__ void fft_pencil(Load ld, Store st, cx<R>* lds, int ls
     if (tvalid && t == 0) st(0, ld(0));
     if constexpr (STLDS) __syncthreads();
   } else {
-    fft_stages<R, L, T, DIR, 1, 0, true, LDLDS, STLDS>(ld, st, lds, ls, t, tvalid, tw, rad{});
+    fft_stages<R, L, T, DIR, PAD, 1, 0, true, LDLDS, STLDS>(ld, st, lds, ls, t, tvalid, tw, rad{});
   }
 }
 
 // The same with the twiddles fetched on the spot.
-template <typename R, int L, int T, int DIR, bool LDLDS = false, bool STLDS = false, class Load, class Store>
+template <typename R, int L, int T, int DIR, bool LDLDS = false, bool STLDS = false, int PAD = PAD_NONE, class Load,
+          class Store>
 __device__ __forceinline__ void fft_pencil(Load ld, Store st, cx<R>* lds, int ls, int t, bool tvalid,
                                            const cx<R>* __restrict__ tw) {
   const TwRegs<R, L, T> w(tw, t);
-  fft_pencil<R, L, T, DIR, LDLDS, STLDS>(ld, st, lds, ls, t, tvalid, w);
+  fft_pencil<R, L, T, DIR, LDLDS, STLDS, PAD>(ld, st, lds, ls, t, tvalid, w);
 }
 
 }  // namespace vie

@@ -125,21 +125,22 @@ __global__ void __launch_bounds__((Geo<R, L>::T * Geo<R, L>::ROWP)) k_row_fwd(Ro
         const bool off = ci.x == 0.0 && ci.y == 0.0;
         return cvt<R>(mk<double>(off ? 0.0 : v.x, off ? 0.0 : v.y));
       };
-      fft_pencil<R, L, T, -1>(ld, st, slot, 1, t, valid, tw);
+      fft_pencil<R, L, T, -1, false, false, PAD_IN>(ld, st, slot, 1, t, valid, tw);
     } else {
       auto ld = [&](int n) -> cx<R> {
         c128 v = mk<double>(0.0, 0.0);
         if (n < nx) v = xin[n];
         return cvt<R>(v);
       };
-      fft_pencil<R, L, T, -1>(ld, st, slot, 1, t, valid, tw);
+      fft_pencil<R, L, T, -1, false, false, PAD_IN>(ld, st, slot, 1, t, valid, tw);
     }
     return;
   }
   const KState& ks = a.k.st[sys];
   const bool first = mode == 1 && ks.iters == 0;
   double acc = 0.0;
-  constexpr int E = (L + T - 1) / T;   // elements per thread
+  constexpr int LH = half_padded(L);     // elements that the transform reads
+  constexpr int E = (LH + T - 1) / T;   // per thread
   constexpr int CH = 4;                // elements per load batch
   c128 rv[CH], pv[CH], vv[CH];
   auto load = [&](int j0) {
@@ -167,7 +168,7 @@ __global__ void __launch_bounds__((Geo<R, L>::T * Geo<R, L>::ROWP)) k_row_fwd(Ro
 #pragma unroll
     for (int u = 0; u < CH; ++u) {
       const int n = t + (j0 + u) * T;
-      if (valid && j0 + u < E && n < L) {
+      if (valid && j0 + u < E && n < LH) {
         if (n < nx) {
           c128 val;
           if (mode == 1)
@@ -185,7 +186,7 @@ __global__ void __launch_bounds__((Geo<R, L>::T * Geo<R, L>::ROWP)) k_row_fwd(Ro
   }
   __syncthreads();
   auto ld = [&](int n) -> cx<R> { return slot[n]; };
-  fft_pencil<R, L, T, -1, true, false>(ld, st, slot, 1, t, valid, tw);
+  fft_pencil<R, L, T, -1, true, false, PAD_IN>(ld, st, slot, 1, t, valid, tw);
   if (mode == 2) {
     double sum[1] = {acc};
     write_partial<1>(sum, a.k.partials, a.k.pstride, a.k.ntile, sys, tile, tiles);
@@ -223,7 +224,7 @@ __global__ void __launch_bounds__((Geo<R, L>::T * Geo<R, L>::ROWP)) k_row_inv_lo
   const double scale = a.scale;
   const int mode = a.out_mode;
   double acc[4] = {0.0, 0.0, 0.0, 0.0};
-  constexpr int E = (L + T - 1) / T;
+  constexpr int E = (half_padded(L) + T - 1) / T;
   constexpr int CH = 4;
   c128 ci[CH], xv[CH], ov[CH];
   auto load = [&](int j0) {
@@ -241,7 +242,7 @@ __global__ void __launch_bounds__((Geo<R, L>::T * Geo<R, L>::ROWP)) k_row_inv_lo
   const TwRegs<R, L, T> tw(a.tw, t);
   constexpr bool EARLY = E <= 2 * CH;   // the operands in flight during the transform, where it holds few values
   if (EARLY) load(0);
-  fft_pencil<R, L, T, +1, false, true>(ld, sts, slot, 1, t, valid, tw);
+  fft_pencil<R, L, T, +1, false, true, PAD_OUT>(ld, sts, slot, 1, t, valid, tw);
 
 #pragma unroll
   for (int j0 = 0; j0 < E; j0 += CH) {
@@ -322,8 +323,8 @@ __global__ void __launch_bounds__((PlaneGeo<R, L, PV>::BT)) k_plane_fwd(RowArgs<
   const int mode = a.in_mode;
   double acc = 0.0;
   const TwRegs<R, L, T> tw(a.tw, threadIdx.x / PP);
-  // zero the padding columns [nx, L) of rows y < ny
-  const int padw = L - nx;
+  // zero the padding columns that the transform reads, [nx, L/2), of rows y < ny
+  const int padw = half_padded(L) - nx;
   for (int e = threadIdx.x; e < npl * ny * padw; e += BT) {
     const int row = e / padw, xx = nx + (e - row * padw);
     const int q = (int)udiv_m((unsigned)row, a.m_ny);
@@ -420,7 +421,7 @@ __global__ void __launch_bounds__((PlaneGeo<R, L, PV>::BT)) k_plane_fwd(RowArgs<
       cx<R>* slot = lds + (rq * L + (rr - rq * ny)) * LP;
       auto ld = [&](int n) -> cx<R> { return slot[n]; };
       auto st = [&](int k, cx<R> v) { slot[k] = v; };
-      fft_pencil<R, L, T, -1, true, true>(ld, st, slot, 1, t, valid, tw);
+      fft_pencil<R, L, T, -1, true, true, PAD_IN>(ld, st, slot, 1, t, valid, tw);
     }
   }
   // y transforms of the L columns (rows >= ny are zero), out to HBM
@@ -437,7 +438,7 @@ __global__ void __launch_bounds__((PlaneGeo<R, L, PV>::BT)) k_plane_fwd(RowArgs<
       cx<R>* wc = w + (int64_t)q * L * L + xq;
       auto ld = [&](int n) -> cx<R> { return n < ny ? slot[n * LP] : czero<R>(); };
       auto st = [&](int k, cx<R> v) { wc[k * L] = v; };
-      fft_pencil<R, L, T, -1, true, false>(ld, st, slot, LP, t, valid, tw);
+      fft_pencil<R, L, T, -1, true, false, PAD_IN>(ld, st, slot, LP, t, valid, tw);
     }
   }
   if (mode == 2) {
@@ -496,7 +497,7 @@ __global__ void __launch_bounds__((PlaneGeo<R, L, PV>::BT)) k_plane_inv_local(Ro
       auto st = [&](int k, cx<R> v) {
         if (k < ny) slot[k * LP] = v;
       };
-      fft_pencil<R, L, T, +1, false, true>(ld, st, slot, LP, t, valid, tw);
+      fft_pencil<R, L, T, +1, false, true, PAD_OUT>(ld, st, slot, LP, t, valid, tw);
     }
   }
   // x inverse of the rows y < ny, in place, cropped to nx (lanes over rows
@@ -514,7 +515,7 @@ __global__ void __launch_bounds__((PlaneGeo<R, L, PV>::BT)) k_plane_inv_local(Ro
       auto st = [&](int k, cx<R> v) {
         if (k < nx) slot[k] = v;
       };
-      fft_pencil<R, L, T, +1, true, true>(ld, st, slot, 1, t, valid, tw);
+      fft_pencil<R, L, T, +1, true, true, PAD_OUT>(ld, st, slot, 1, t, valid, tw);
     }
   }
   // y = x/chi - scale Q on the mask, fused inner products
@@ -586,7 +587,7 @@ struct ColArgs {
   int nsys;
 };
 
-template <typename R, int L, int DIR>
+template <typename R, int L, int DIR, int PAD>
 __global__ void __launch_bounds__((Geo<R, L>::TC * Geo<R, L>::COLP)) k_col(ColArgs<R> a) {
   using G = Geo<R, L>;
   __shared__ cx<R> lds[G::COLP * L];
@@ -607,7 +608,7 @@ __global__ void __launch_bounds__((Geo<R, L>::TC * Geo<R, L>::COLP)) k_col(ColAr
     if (k < n_out) base[(int64_t)k * inner] = v;
   };
   const TwRegs<R, L, G::TC> tw(a.tw, t);
-  fft_pencil<R, L, G::TC, DIR>(ld, st, lds + p, G::COLP, t, valid, tw);
+  fft_pencil<R, L, G::TC, DIR, false, false, PAD>(ld, st, lds + p, G::COLP, t, valid, tw);
 }
 
 // ------------------------------------------------------------------ launchers
@@ -647,7 +648,7 @@ static void launch_row_inv(int L, const RowArgs<R>& a, int nsys, hipStream_t s) 
   check_launch("x inverse");
 }
 
-template <typename R, int DIR>
+template <typename R, int DIR, int PAD>
 static void launch_col(int L, const ColArgs<R>& a, hipStream_t s) {
   switch (L) {
 #define C(l)                                                                        \
@@ -655,7 +656,7 @@ static void launch_col(int L, const ColArgs<R>& a, hipStream_t s) {
     using G = Geo<R, l>;                                                            \
     const int64_t cols = (int64_t)a.outer * a.inner;                                \
     const int64_t tiles = (cols + G::COLP - 1) / G::COLP;                           \
-    hipLaunchKernelGGL((k_col<R, l, DIR>), dim3((unsigned)(tiles * a.nsys)), dim3(G::TC * G::COLP), 0, s, a); \
+    hipLaunchKernelGGL((k_col<R, l, DIR, PAD>), dim3((unsigned)(tiles * a.nsys)), dim3(G::TC * G::COLP), 0, s, a); \
     break;                                                                          \
   }
     VIE_L_CASES(C)
@@ -718,9 +719,17 @@ static void mark(hipEvent_t* ev, int i, hipStream_t s) {
   if (ev && hipEventRecord(ev[i], s) != hipSuccess) throw std::runtime_error("hipEventRecord failed");
 }
 
+// The products' transforms take padded axes to be at least half empty.
+static void check_padding(int n, int l) {
+  if (n < 1 || n > half_padded(l)) throw std::runtime_error("transform length below twice the axis");
+}
+
 template <typename R>
 static RowArgs<R> row_args(const MvmBatch<R>& b, const KBatch* k, const FuseArgs& f, const c128* x, c128* y,
                            bool mask_input) {
+  check_padding(b.nx, b.lx);
+  check_padding(b.ny, b.ly);
+  check_padding(b.nz, b.lz);
   RowArgs<R> ra{};
   ra.nx = b.nx;
   ra.ny = b.ny;
@@ -770,6 +779,8 @@ void mvm_pass1(const MvmBatch<R>& b, const KBatch* k, const FuseArgs& f, const c
 template <typename R>
 void mvm_mid(const MvmBatch<R>& b, hipStream_t s) {
   if (b.nsys <= 0) return;
+  check_padding(b.ny, b.ly);
+  check_padding(b.nz, b.lz);
   ColArgs<R> ca{};
   ca.data = b.work;
   ca.outer = 3 * b.nz;
@@ -780,7 +791,7 @@ void mvm_mid(const MvmBatch<R>& b, hipStream_t s) {
   ca.status = b.status;
   ca.tw = b.tw->table[b.ly];
   ca.nsys = b.nsys;
-  if (!b.plane) launch_col<R, -1>(b.ly, ca, s);
+  if (!b.plane) launch_col<R, -1, PAD_IN>(b.ly, ca, s);
 
   ZArgs<R> za{};
   za.nz = b.nz;
@@ -799,7 +810,7 @@ void mvm_mid(const MvmBatch<R>& b, hipStream_t s) {
 
   ca.n_in = b.ly;
   ca.n_out = b.ny;
-  if (!b.plane) launch_col<R, +1>(b.ly, ca, s);
+  if (!b.plane) launch_col<R, +1, PAD_OUT>(b.ly, ca, s);
 }
 
 template <typename R>
@@ -839,7 +850,7 @@ void mvm(const MvmBatch<R>& b, const c128* x, c128* y, bool mask_input, hipStrea
     ca.status = b.status;
     ca.tw = b.tw->table[b.ly];
     ca.nsys = b.nsys;
-    if (!b.plane) launch_col<R, -1>(b.ly, ca, s);
+    if (!b.plane) launch_col<R, -1, PAD_IN>(b.ly, ca, s);
     mark(ev, 2, s);
     ZArgs<R> za{};
     za.nz = b.nz;
@@ -858,7 +869,7 @@ void mvm(const MvmBatch<R>& b, const c128* x, c128* y, bool mask_input, hipStrea
     mark(ev, 3, s);
     ca.n_in = b.ly;
     ca.n_out = b.ny;
-    if (!b.plane) launch_col<R, +1>(b.ly, ca, s);
+    if (!b.plane) launch_col<R, +1, PAD_OUT>(b.ly, ca, s);
     mark(ev, 4, s);
   }
   mvm_pass5<R>(b, nullptr, none, x, y, s);
@@ -866,17 +877,18 @@ void mvm(const MvmBatch<R>& b, const c128* x, c128* y, bool mask_input, hipStrea
 }
 
 // The z-pass variant of a shape; `cols` counts the columns of every system of
-// the batch.  Measured with the kernels alone (f32 / f64, us; small: 1024
-// columns, large: 65536):
-//   length   32: V4 4.1 / 4.3 small; large V3 16.1 f32 (V4 19.0), V4 27.7 f64 (V3 30.4)
-//            36: V2 4.5, V4 5.2 small; large V3 30.9 / 42.7 (V2 41.5, V4 45.1)
-//            48: V0 5.5, V4 6.0 small; large V2 28.2 / 47.5 (V0 42.5 / 99.5)
-//            64: V4 5.1 / 5.2; large V4 29.1 / 46.3 (V3 31.4 / 59.6)
-//            72: V2 6.1, V0 5.8 small; large V2 51.0 (V4 54.6), V3 80.7 (V0 113.6)
-//            96: V0 6.7 / 6.5 small; large V2 56.3 (V0 62.8), V0 113.4 (V2 133.0);
-//                rooftop f64 V3 115 (V0 163)
-//           128: V4 6.7 / 7.2; large V4 66.6 / 163.4 (V2 82.4 / 194.4); rooftop f64 V3 109.5 (V4 129)
-//   from 144 on V4 (V0 equal, V2 and V3 slower); below 32 V0 and V4 are one.
+// the batch.  Measured with the kernels alone, 5 us of event overhead with
+// them (f32 / f64, us; small: 1024 columns, large: 65536):
+//   length   32: V4 6.8 / 8.5 small; large V3 21.2 f32 (V4 24.0), V4 31.4 f64 (V3 34.9)
+//            36: V2 7.6, V4 7.2 / 8.1 small; large V3 35.4 / 46.9 (V2 45.6, V4 48.1)
+//            48: V0 7.8, V4 8.4 / 9.2 small; large V2 33.6 / 53.9 (V0 47.4 / 97.8)
+//            64: V4 7.8 / 8.4 small; large V4 34.8 / 51.3 (V3 38.2 / 66.9)
+//            72: V2 8.7, V0 8.5 / 8.5 small; large V2 57.8 (V4 59.6), V3 85.9 (V0 112.4)
+//            96: V0 9.0 / 10.3 small; large V2 64.4 (V0 71.7), V0 138.8 (V2 153.4)
+//           128: V4 10.5 / 10.5 small; large V4 81.1 / 169.4 (V2 96.2 / 203.3);
+//                rooftop f64 V3 27.1 (V4 34.8) from 9216 columns, 132.6 (V4 200.4) large
+//           144: V4 11.7 / 12.5 small; large V4 118.9 (V3 143.8), V3 271.7 (V4 299.2)
+//   from 192 on V4 (V0 equal, V2 and V3 slower); below 32 V0 and V4 are one.
 // The mirror columns (V1) were ahead in none of 96 shapes of lengths 4 to 256.
 // The lines between small and large lie where the two variants cross.
 int zpass_rule(int elem_bytes, int lz, bool rooftop, int64_t cols) {
@@ -887,10 +899,9 @@ int zpass_rule(int elem_bytes, int lz, bool rooftop, int64_t cols) {
     case 36: return f32 ? (cols >= 16384 ? 3 : 2) : (cols >= 32768 ? 3 : 4);
     case 48: return cols >= 8192 ? 2 : (f32 ? 0 : 4);
     case 72: return f32 ? 2 : (cols >= 8192 ? 3 : 0);
-    case 96:
-      if (f32) return cols >= 16384 ? 2 : 0;
-      return rooftop ? (cols >= 16384 ? 3 : 2) : 0;
-    case 128: return !f32 && rooftop && cols >= 32768 ? 3 : 4;
+    case 96: return f32 && cols >= 16384 ? 2 : 0;
+    case 128: return !f32 && rooftop && cols >= 8192 ? 3 : 4;
+    case 144: return !f32 && cols >= 8192 ? 3 : 4;
     default: return 4;
   }
 }
@@ -1075,13 +1086,13 @@ void green_spectra(int nx, int ny, int nz, int lx, int ly, int lz, double dx, do
   ca.status = nullptr;
   ca.tw = tw.table[ly];
   ca.nsys = 1;
-  launch_col<double, -1>(ly, ca, s);
+  launch_col<double, -1, PAD_NONE>(ly, ca, s);
   ca.outer = 6;
   ca.inner = lx * ly;
   ca.n_in = lz;
   ca.n_out = lz;
   ca.tw = tw.table[lz];
-  launch_col<double, -1>(lz, ca, s);
+  launch_col<double, -1, PAD_NONE>(lz, ca, s);
   const int64_t oct = 6 * (int64_t)(lx / 2 + 1) * (ly / 2 + 1) * (lz / 2 + 1);
   hipLaunchKernelGGL(k_extract_octant, dim3((unsigned)((oct + 255) / 256)), dim3(256), 0, s, scratch, spec64, spec32,
                      lx, ly, lz, 6);
@@ -1173,13 +1184,13 @@ void green_spectrum_rooftop(int nx, int ny, int nz, int lx, int ly, int lz, doub
   ca.status = nullptr;
   ca.tw = tw.table[ly];
   ca.nsys = 1;
-  launch_col<double, -1>(ly, ca, s);
+  launch_col<double, -1, PAD_NONE>(ly, ca, s);
   ca.outer = 1;
   ca.inner = lx * ly;
   ca.n_in = lz;
   ca.n_out = lz;
   ca.tw = tw.table[lz];
-  launch_col<double, -1>(lz, ca, s);
+  launch_col<double, -1, PAD_NONE>(lz, ca, s);
   const int64_t oct = (int64_t)(lx / 2 + 1) * (ly / 2 + 1) * (lz / 2 + 1);
   hipLaunchKernelGGL(k_extract_octant, dim3((unsigned)((oct + 255) / 256)), dim3(256), 0, s, scratch, spec64, spec32,
                      lx, ly, lz, 1);

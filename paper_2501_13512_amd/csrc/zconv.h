@@ -66,6 +66,10 @@ struct ZColGeo {
   // prefetched spectrum (64 systems of length 48: 49 us without, 60 with) or
   // for short columns
   static constexpr bool HOLD = sizeof(R) == 4 || (!PF && LZ >= 72);
+  // wavefronts per SIMD that the registers must leave room for: FP64 beside
+  // the prefetched spectrum needs the third (64 systems of length 48: 48 us
+  // with three, 67 with the two that 170 registers allow)
+  static constexpr int WAVES = sizeof(R) == 8 && PF && LZ <= 64 ? 3 : 1;
 };
 
 // Variant 1 (mirror columns): geometry.
@@ -107,7 +111,7 @@ __global__ void __launch_bounds__((3 * ZGeo<R, LZ>::T * ZGeo<R, LZ>::ZP)) k_zcon
     cx<R>* slot = lds + (m * 3 + comp) * SLOT + p;
     auto ldg = [&](int n) -> cx<R> { return n < nz ? base[n * plane] : czero<R>(); };
     auto sts = [&](int k, cx<R> v) { slot[k * ZP] = v; };
-    fft_pencil<R, LZ, T, -1, false, true>(ldg, sts, slot, ZP, t, valid, a.tw);
+    fft_pencil<R, LZ, T, -1, false, true, PAD_IN>(ldg, sts, slot, ZP, t, valid, a.tw);
   }
 
   // Q = S X at every point of the four columns; one spectrum load per
@@ -163,7 +167,7 @@ __global__ void __launch_bounds__((3 * ZGeo<R, LZ>::T * ZGeo<R, LZ>::ZP)) k_zcon
     auto stg = [&](int k, cx<R> v) {
       if (k < nz) base[k * plane] = v;
     };
-    fft_pencil<R, LZ, T, +1, true, false>(lds_ld, stg, slot, ZP, t, valid, a.tw);
+    fft_pencil<R, LZ, T, +1, true, false, PAD_OUT>(lds_ld, stg, slot, ZP, t, valid, a.tw);
   }
 }
 
@@ -175,7 +179,8 @@ __global__ void __launch_bounds__((3 * ZGeo<R, LZ>::T * ZGeo<R, LZ>::ZP)) k_zcon
 // the face gradient of cell values.  The spectrum buffer holds the octant of
 // G' followed by the full-length tables b_x[lx], b_y[ly], b_z[lz].
 template <typename R, int LZ, int V, int K>
-__global__ void __launch_bounds__((3 * ZColGeo<R, LZ, V>::TZ * ZColGeo<R, LZ, V>::ZP)) k_zconv_col(ZArgs<R> a) {
+__global__ void __launch_bounds__((3 * ZColGeo<R, LZ, V>::TZ * ZColGeo<R, LZ, V>::ZP), (ZColGeo<R, LZ, V>::WAVES))
+    k_zconv_col(ZArgs<R> a) {
   using G = ZColGeo<R, LZ, V>;
   constexpr int T = G::TZ, ZP = G::ZP;
   constexpr int NT = 3 * T * ZP;
@@ -276,7 +281,7 @@ __global__ void __launch_bounds__((3 * ZColGeo<R, LZ, V>::TZ * ZColGeo<R, LZ, V>
     return n < nz ? *elem(wsys, toff + (unsigned)(n - t) * plane) : czero<R>();
   };
   auto sts = [&](int k, cx<R> v) { slot[k * ZP] = v; };
-  fft_pencil<R, LZ, T, -1, false, true>(ldg, sts, slot, ZP, t, valid, tw);
+  fft_pencil<R, LZ, T, -1, false, true, PAD_IN>(ldg, sts, slot, ZP, t, valid, tw);
 
   // Q(q) = S(q) X(q), S symmetric 3x3 from the octant with parity signs
   if constexpr (K == 1) if (cvalid) {
@@ -340,7 +345,7 @@ __global__ void __launch_bounds__((3 * ZColGeo<R, LZ, V>::TZ * ZColGeo<R, LZ, V>
   auto stg = [&](int k, cx<R> v) {
     if (k < nz) *elem(wsys, toff + (unsigned)(k - t) * plane) = v;
   };
-  fft_pencil<R, LZ, T, +1, true, false>(lds_ld, stg, slot, ZP, t, valid, tw);
+  fft_pencil<R, LZ, T, +1, true, false, PAD_OUT>(lds_ld, stg, slot, ZP, t, valid, tw);
 }
 
 template <typename R, int L, int V>
