@@ -163,12 +163,14 @@ template <class Rad>
 struct RadInfo;
 template <>
 struct RadInfo<Radices<>> {
+  static constexpr int first = 1;
   static constexpr int nstages = 0;
   static constexpr int rmin = 1 << 30;
   static constexpr int rmax = 1;
 };
 template <int R0, int... Rs>
 struct RadInfo<Radices<R0, Rs...>> {
+  static constexpr int first = R0;
   static constexpr int nstages = 1 + sizeof...(Rs);
   static constexpr int rmin = R0 < RadInfo<Radices<Rs...>>::rmin ? R0 : RadInfo<Radices<Rs...>>::rmin;
   static constexpr int rmax = R0 > RadInfo<Radices<Rs...>>::rmax ? R0 : RadInfo<Radices<Rs...>>::rmax;
@@ -255,6 +257,20 @@ enum Pad { PAD_NONE = 0, PAD_IN = 1, PAD_OUT = 2 };
 // elements of a padded pencil that can be voxels
 __host__ __device__ constexpr int half_padded(int l) { return l % 2 == 0 ? l / 2 : (l + 1) / 2; }
 
+// Place of element i of a pencil in its LDS slot: consecutive elements LS
+// apart, or, for pencils that lie along their lanes (rows), one element left
+// out after every RAD.  A stage's butterflies write RAD elements apart, which
+// without the gaps is the same banks for all lanes (rows of length 256: 28
+// conflict cycles per LDS instruction; the 128x128x32 FP64 product took 176 us
+// with them and takes 171).
+template <int RAD>
+struct RowSlot {};
+__device__ __forceinline__ int slot_at(int ls, int i) { return i * ls; }
+template <int RAD>
+__device__ __forceinline__ int slot_at(RowSlot<RAD>, int i) {
+  return RAD > 1 ? i + i / RAD : i;
+}
+
 // One stage.  Threads t < T of a pencil cooperate; `lds` points at element 0
 // of this pencil's LDS slot and consecutive elements are `ls` apart.  All
 // threads of the workgroup must call every stage (barriers inside).
@@ -262,8 +278,8 @@ __host__ __device__ constexpr int half_padded(int l) { return l % 2 == 0 ? l / 2
 // it.  Then the first (last) stage separates its reads from its writes by a
 // barrier, since the transform runs in place in the slot.
 template <typename R, int L, int T, int DIR, int PAD, int RAD, int P, int AT, bool FIRST, bool LAST, bool LDLDS,
-          bool STLDS, class Load, class Store, bool HOLD>
-__device__ __forceinline__ void fft_stage(Load& ld, Store& st, cx<R>* lds, int ls, int t, bool tvalid,
+          bool STLDS, class Load, class Store, class Slot, bool HOLD>
+__device__ __forceinline__ void fft_stage(Load& ld, Store& st, cx<R>* lds, Slot ls, int t, bool tvalid,
                                           const TwRegs<R, L, T, HOLD>& tw) {
   constexpr int NB = L / RAD;
   constexpr int NPT = (NB + T - 1) / T;
@@ -284,7 +300,7 @@ __device__ __forceinline__ void fft_stage(Load& ld, Store& st, cx<R>* lds, int l
         if constexpr (FIRST)
           v[q][m] = ld(idx);
         else
-          v[q][m] = lds[idx * ls];
+          v[q][m] = lds[slot_at(ls, idx)];
       }
     }
   }
@@ -305,7 +321,7 @@ __device__ __forceinline__ void fft_stage(Load& ld, Store& st, cx<R>* lds, int l
         if constexpr (LAST)
           st(j + m * P, v[q][m]);
         else
-          lds[(j + m * P) * ls] = v[q][m];
+          lds[slot_at(ls, j + m * P)] = v[q][m];
       }
     }
   }
@@ -313,8 +329,8 @@ __device__ __forceinline__ void fft_stage(Load& ld, Store& st, cx<R>* lds, int l
 }
 
 template <typename R, int L, int T, int DIR, int PAD, int P, int AT, bool FIRST, bool LDLDS, bool STLDS, class Load,
-          class Store, bool HOLD, int RAD, int... Rest>
-__device__ __forceinline__ void fft_stages(Load& ld, Store& st, cx<R>* lds, int ls, int t, bool tvalid,
+          class Store, class Slot, bool HOLD, int RAD, int... Rest>
+__device__ __forceinline__ void fft_stages(Load& ld, Store& st, cx<R>* lds, Slot ls, int t, bool tvalid,
                                            const TwRegs<R, L, T, HOLD>& tw, Radices<RAD, Rest...>) {
   constexpr bool LAST = sizeof...(Rest) == 0;
   constexpr int NEXT = AT + (P > 1 ? (RAD - 1) * ((L / RAD + T - 1) / T) : 0);
@@ -329,8 +345,8 @@ __device__ __forceinline__ void fft_stages(Load& ld, Store& st, cx<R>* lds, int 
 // buffer between stages; see fft_stage for LDLDS / STLDS.  With PAD_IN (even
 // L) ld is not asked for n >= L/2; with PAD_OUT st may not be given k >= L/2.
 template <typename R, int L, int T, int DIR, bool LDLDS = false, bool STLDS = false, int PAD = PAD_NONE, class Load,
-          class Store, bool HOLD>
-__device__ __forceinline__ void fft_pencil(Load ld, Store st, cx<R>* lds, int ls, int t, bool tvalid,
+          class Store, class Slot, bool HOLD>
+__device__ __forceinline__ void fft_pencil(Load ld, Store st, cx<R>* lds, Slot ls, int t, bool tvalid,
                                            const TwRegs<R, L, T, HOLD>& tw) {
   using rad = typename Plan<L>::type;
   if constexpr (RadInfo<rad>::nstages == 0) {
@@ -343,8 +359,8 @@ __device__ __forceinline__ void fft_pencil(Load ld, Store st, cx<R>* lds, int ls
 
 // The same with the twiddles fetched on the spot.
 template <typename R, int L, int T, int DIR, bool LDLDS = false, bool STLDS = false, int PAD = PAD_NONE, class Load,
-          class Store>
-__device__ __forceinline__ void fft_pencil(Load ld, Store st, cx<R>* lds, int ls, int t, bool tvalid,
+          class Store, class Slot>
+__device__ __forceinline__ void fft_pencil(Load ld, Store st, cx<R>* lds, Slot ls, int t, bool tvalid,
                                            const cx<R>* __restrict__ tw) {
   const TwRegs<R, L, T> w(tw, t);
   fft_pencil<R, L, T, DIR, LDLDS, STLDS, PAD>(ld, st, lds, ls, t, tvalid, w);

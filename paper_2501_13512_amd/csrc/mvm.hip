@@ -41,6 +41,9 @@ struct Geo {
   static constexpr int ES = (int)sizeof(cx<R>);
   // rows (contiguous pencils): ~256 threads, LDS [ROWP][L]
   static constexpr int ROWP = cmax(1, cmin(256 / T, (64 * 1024) / (L * ES)));
+  static constexpr int RAD0 = RadInfo<typename Plan<L>::type>::first;
+  using RS = RowSlot<RAD0>;                                  // rows with gaps against bank conflicts
+  static constexpr int ROWL = RAD0 > 1 ? L + L / RAD0 : L;
   // columns (strided pencils), LDS [L][COLP]: at least 128 contiguous bytes
   // per row of the tile (one full cache line) when 64 KB of LDS allow it,
   // with TC <= T threads per column (several butterflies per thread when
@@ -91,8 +94,9 @@ struct RowArgs {
 template <typename R, int L>
 __global__ void __launch_bounds__((Geo<R, L>::T * Geo<R, L>::ROWP)) k_row_fwd(RowArgs<R> a) {
   using G = Geo<R, L>;
+  using RS = typename G::RS;
   constexpr int T = G::T;
-  __shared__ cx<R> lds[G::ROWP * L];
+  __shared__ cx<R> lds[G::ROWP * G::ROWL];
   const int rows = 3 * a.nz * a.ny;
   const int tiles = (rows + G::ROWP - 1) / G::ROWP;
   const int sys = blockIdx.x / tiles, tile = blockIdx.x - sys * tiles;
@@ -105,7 +109,7 @@ __global__ void __launch_bounds__((Geo<R, L>::T * Geo<R, L>::ROWP)) k_row_fwd(Ro
   const int z = zy / a.ny, yy = zy - z * a.ny;
   const int64_t vrow = sys * a.vstride + (int64_t)rr * a.nx;
   cx<R>* w = a.work + sys * a.wstride + ((int64_t)(c * a.nz + z) * a.ly + yy) * a.lx;
-  cx<R>* slot = lds + p * L;
+  cx<R>* slot = lds + p * G::ROWL;
   const int nx = a.nx;
   const int mode = a.in_mode;
   const TwRegs<R, L, T> tw(a.tw, t);
@@ -125,14 +129,14 @@ __global__ void __launch_bounds__((Geo<R, L>::T * Geo<R, L>::ROWP)) k_row_fwd(Ro
         const bool off = ci.x == 0.0 && ci.y == 0.0;
         return cvt<R>(mk<double>(off ? 0.0 : v.x, off ? 0.0 : v.y));
       };
-      fft_pencil<R, L, T, -1, false, false, PAD_IN>(ld, st, slot, 1, t, valid, tw);
+      fft_pencil<R, L, T, -1, false, false, PAD_IN>(ld, st, slot, RS(), t, valid, tw);
     } else {
       auto ld = [&](int n) -> cx<R> {
         c128 v = mk<double>(0.0, 0.0);
         if (n < nx) v = xin[n];
         return cvt<R>(v);
       };
-      fft_pencil<R, L, T, -1, false, false, PAD_IN>(ld, st, slot, 1, t, valid, tw);
+      fft_pencil<R, L, T, -1, false, false, PAD_IN>(ld, st, slot, RS(), t, valid, tw);
     }
     return;
   }
@@ -176,17 +180,17 @@ __global__ void __launch_bounds__((Geo<R, L>::T * Geo<R, L>::ROWP)) k_row_fwd(Ro
           else
             val = rv[u] - c1 * vv[u];                                    // s = r - alpha v
           a.p[vrow + n] = val;
-          slot[n] = cvt<R>(val);
+          slot[slot_at(RS(), n)] = cvt<R>(val);
           acc += abs2(val);
         } else {
-          slot[n] = czero<R>();
+          slot[slot_at(RS(), n)] = czero<R>();
         }
       }
     }
   }
   __syncthreads();
-  auto ld = [&](int n) -> cx<R> { return slot[n]; };
-  fft_pencil<R, L, T, -1, true, false, PAD_IN>(ld, st, slot, 1, t, valid, tw);
+  auto ld = [&](int n) -> cx<R> { return slot[slot_at(RS(), n)]; };
+  fft_pencil<R, L, T, -1, true, false, PAD_IN>(ld, st, slot, RS(), t, valid, tw);
   if (mode == 2) {
     double sum[1] = {acc};
     write_partial<1>(sum, a.k.partials, a.k.pstride, a.k.ntile, sys, tile, tiles);
@@ -200,8 +204,9 @@ __global__ void __launch_bounds__((Geo<R, L>::T * Geo<R, L>::ROWP)) k_row_fwd(Ro
 template <typename R, int L>
 __global__ void __launch_bounds__((Geo<R, L>::T * Geo<R, L>::ROWP)) k_row_inv_local(RowArgs<R> a) {
   using G = Geo<R, L>;
+  using RS = typename G::RS;
   constexpr int T = G::T;
-  __shared__ cx<R> lds[G::ROWP * L];
+  __shared__ cx<R> lds[G::ROWP * G::ROWL];
   const int rows = 3 * a.nz * a.ny;
   const int tiles = (rows + G::ROWP - 1) / G::ROWP;
   const int sys = blockIdx.x / tiles, tile = blockIdx.x - sys * tiles;
@@ -215,11 +220,11 @@ __global__ void __launch_bounds__((Geo<R, L>::T * Geo<R, L>::ROWP)) k_row_inv_lo
   const int64_t vrow = sys * a.vstride + (int64_t)rr * a.nx;
   const c128* chi = a.chi_inv + sys * a.cstride + (int64_t)(a.chi3 ? rr : zy) * a.nx;
   const cx<R>* w = a.work + sys * a.wstride + ((int64_t)(c * a.nz + z) * a.ly + yy) * a.lx;
-  cx<R>* slot = lds + p * L;
+  cx<R>* slot = lds + p * G::ROWL;
   const int nx = a.nx;
   auto ld = [&](int n) -> cx<R> { return w[n]; };
   auto sts = [&](int k, cx<R> v) {
-    if (k < nx) slot[k] = v;
+    if (k < nx) slot[slot_at(RS(), k)] = v;
   };
   const double scale = a.scale;
   const int mode = a.out_mode;
@@ -242,7 +247,7 @@ __global__ void __launch_bounds__((Geo<R, L>::T * Geo<R, L>::ROWP)) k_row_inv_lo
   const TwRegs<R, L, T> tw(a.tw, t);
   constexpr bool EARLY = E <= 2 * CH;   // the operands in flight during the transform, where it holds few values
   if (EARLY) load(0);
-  fft_pencil<R, L, T, +1, false, true, PAD_OUT>(ld, sts, slot, 1, t, valid, tw);
+  fft_pencil<R, L, T, +1, false, true, PAD_OUT>(ld, sts, slot, RS(), t, valid, tw);
 
 #pragma unroll
   for (int j0 = 0; j0 < E; j0 += CH) {
@@ -253,9 +258,9 @@ __global__ void __launch_bounds__((Geo<R, L>::T * Geo<R, L>::ROWP)) k_row_inv_lo
       if (valid && j0 + u < E && k < nx) {
         c128 out = mk<double>(0.0, 0.0);
         if (mode == 3)   // field at every voxel: E_inc + sum T P
-          out = ov[u] + scale * cvt<double>(slot[k]);
+          out = ov[u] + scale * cvt<double>(slot[slot_at(RS(), k)]);
         else if (ci[u].x != 0.0 || ci[u].y != 0.0)
-          out = xv[u] * ci[u] - scale * cvt<double>(slot[k]);
+          out = xv[u] * ci[u] - scale * cvt<double>(slot[slot_at(RS(), k)]);
         a.y[vrow + k] = out;
         if (mode == 1) {          // <rhat, y>
           const c128 d = cdot1(ov[u], out);
@@ -564,14 +569,14 @@ template <typename R, int L>
 __global__ void __launch_bounds__((Geo<R, L>::T * Geo<R, L>::ROWP)) k_row_full(cx<R>* data, int64_t rows,
                                                                            const cx<R>* tw) {
   using G = Geo<R, L>;
-  __shared__ cx<R> lds[G::ROWP * L];
+  __shared__ cx<R> lds[G::ROWP * G::ROWL];
   const int p = threadIdx.x / G::T, t = threadIdx.x - p * G::T;
   const int64_t row = (int64_t)blockIdx.x * G::ROWP + p;
   const bool valid = row < rows;
   cx<R>* d = data + (valid ? row : 0) * L;
   auto ld = [&](int n) -> cx<R> { return d[n]; };
   auto st = [&](int k, cx<R> v) { d[k] = v; };
-  fft_pencil<R, L, G::T, -1>(ld, st, lds + p * L, 1, t, valid, tw);
+  fft_pencil<R, L, G::T, -1>(ld, st, lds + p * G::ROWL, typename G::RS(), t, valid, tw);
 }
 
 // Strided pencils, in place: per system, data[outer][L][inner]; element n of
