@@ -52,7 +52,7 @@ struct MvmBatch {
   const int* status;       // per system; null = always active
   const TwiddleSet<R>* tw; // host-side pointer table (values are device pointers)
   int zvariant;            // z-pass kernel variant (see zpass_rule)
-  int plane;               // 1: x and y transforms fused per z-plane (plane_supported(lx, ly))
+  int plane;               // 1: x and y transforms fused per z-plane (plane_supported)
   int pvariant;            // plane kernels: planes per workgroup variant (see plane_rule)
   // 0: collocated voxels (spec: six octant spectra, 1/chi per voxel);
   // 1: rooftop faces (spec: the scalar octant spectrum and difference
@@ -60,8 +60,8 @@ struct MvmBatch {
   int rooftop;
 };
 
-// Square transforms small enough for the fused plane kernels.
-bool plane_supported(int lx, int ly);
+// Square transforms for the fused plane kernels; planes of all systems.
+bool plane_supported(int lx, int ly, int elem_bytes, int64_t planes);
 
 // y = A x for every active system of the batch (Sec. I Toeplitz + FFT;
 // eqs. (2)-(4)).  `mask_input` zeroes x where 1/chi = 0 before transforming.

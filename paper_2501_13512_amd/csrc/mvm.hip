@@ -288,14 +288,15 @@ __global__ void __launch_bounds__((Geo<R, L>::T * Geo<R, L>::ROWP)) k_row_inv_lo
 }
 
 // ------------------------------------------------------------------ plane passes
-// Small square transforms (lx = ly <= 64): the x and y transforms of a
+// Small square transforms (lx = ly <= 128): the x and y transforms of a
 // z-plane run in one kernel with the plane in LDS, so passes 1 + 2 become
 // k_plane_fwd and passes 4 + 5 become k_plane_inv_local (one launch and one
 // trip through HBM fewer each way; same BiCGSTAB fusion as the row kernels).
 // A workgroup takes NPL consecutive planes (c, z) of one system; LDS holds
 // them as [NPL][L][L + 1] (rows padded against bank conflicts on columns).
 // Variant PV sets NPL: 0 as many planes as 48 KB of LDS hold (at most 16),
-// 1 at most two, 2 one plane.  Fewer planes per workgroup mean more, shorter
+// 1 at most two, 2 one plane.  From 96 on a workgroup is 1024 threads and one
+// plane, the CU's LDS holding no second FP64 one.  Fewer planes per workgroup mean more, shorter
 // workgroups: the product's latency falls when few systems are active (two
 // 32 x 32 planes of a 16 x 16 box take 3 transform rounds of 32 pencils
 // where five planes take 8), at the cost of more workgroups to dispatch.
@@ -303,9 +304,10 @@ template <typename R, int L, int PV>
 struct PlaneGeo {
   static constexpr int ES = (int)sizeof(cx<R>);
   static constexpr int LP = L + 1;
+  static constexpr bool FITS = L * LP * ES <= 150 * 1024;
   static constexpr int NPL_LDS = cmax(1, cmin(16, (48 * 1024) / (L * LP * ES)));
   static constexpr int NPL = PV == 0 ? NPL_LDS : (PV == 1 ? cmin(2, NPL_LDS) : 1);
-  static constexpr int BT = 256;
+  static constexpr int BT = L > 64 ? 1024 : 256;
   static constexpr int T = PlanInfo<L>::max_butterflies;
   static constexpr int PP = BT / T;
   static_assert(BT % T == 0, "pencil threads must divide the workgroup");
@@ -672,10 +674,22 @@ static void launch_col(int L, const ColArgs<R>& a, hipStream_t s) {
   check_launch("column pass");
 }
 
-#define VIE_PLANE_CASES(F) F(8) F(12) F(16) F(24) F(32) F(48) F(64)
+#define VIE_PLANE_SMALL(F) F(8) F(12) F(16) F(24) F(32) F(48) F(64)
+#define VIE_PLANE_CASES(F) VIE_PLANE_SMALL(F) F(96) F(128)
 
-bool plane_supported(int lx, int ly) {
-  if (lx != ly) return false;
+// Whether a batch's x and y transforms run per plane; `planes` as for
+// plane_rule.  Up to 64 always.  A plane of length 96 or 128 takes most of a
+// CU's LDS and 8 to 10 us of its time, so few planes are better spread over
+// the chip as rows and columns: product of 48x48xnz / 64x64xnz, rows and
+// columns against planes, us:
+//   96 f32: nz 16 24.6, 27.3; 32 33.0, 32.3; 48 44.6, 41.1; 64 49.3, 41.1; 128 74.6, 74.7; 256 146, 150
+//      f64: nz 16 31.5, 35.2; 32 42.5, 41.6; 48 54.1, 49.0; 64 61.0, 54.8; 128 108, 108; 256 210, 203
+//  128 f32: nz 16 30.4, 31.1; 32 41.5, 33.9; 48 52.9, 42.7; 64 55.1, 46.2; 128 101, 94; 256 231, 214
+// FP64 planes of length 128 exceed the LDS.
+bool plane_supported(int lx, int ly, int elem_bytes, int64_t planes) {
+  if (lx != ly || lx > 128) return false;
+  if (lx > 64 && (planes < 96 || (lx == 128 && elem_bytes == 8) || (lx == 96 && elem_bytes == 4 && planes > 384)))
+    return false;
 #define C(l) \
   if (lx == l) return true;
   VIE_PLANE_CASES(C)
@@ -687,10 +701,14 @@ template <typename R, int L, int PV>
 static void launch_plane_pv(bool fwd, const RowArgs<R>& a, int nsys, hipStream_t s) {
   using G = PlaneGeo<R, L, PV>;
   const int tiles = (3 * a.nz + G::NPL - 1) / G::NPL;
-  if (fwd)
-    hipLaunchKernelGGL((k_plane_fwd<R, L, PV>), dim3(tiles * nsys), dim3(G::BT), 0, s, a);
-  else
-    hipLaunchKernelGGL((k_plane_inv_local<R, L, PV>), dim3(tiles * nsys), dim3(G::BT), 0, s, a);
+  if constexpr (G::FITS) {
+    if (fwd)
+      hipLaunchKernelGGL((k_plane_fwd<R, L, PV>), dim3(tiles * nsys), dim3(G::BT), 0, s, a);
+    else
+      hipLaunchKernelGGL((k_plane_inv_local<R, L, PV>), dim3(tiles * nsys), dim3(G::BT), 0, s, a);
+  } else {
+    bad_length("plane pass", L);
+  }
 }
 
 template <typename R>
@@ -705,9 +723,9 @@ static void launch_plane(bool fwd, int L, int pv, const RowArgs<R>& a, int nsys,
 #define C(l)                                                 \
   case l: {                                                  \
     if (pv == 0)                                             \
-      launch_plane_pv<R, l, 0>(fwd, a, nsys, s);             \
+      launch_plane_pv<R, l, (l > 64 ? 2 : 0)>(fwd, a, nsys, s); \
     else if (pv == 1)                                        \
-      launch_plane_pv<R, l, 1>(fwd, a, nsys, s);             \
+      launch_plane_pv<R, l, (l > 64 ? 2 : 1)>(fwd, a, nsys, s); \
     else                                                     \
       launch_plane_pv<R, l, 2>(fwd, a, nsys, s);             \
     break;                                                   \
@@ -937,14 +955,14 @@ VIE_MVM_INST(double)
 
 int64_t mvm_row_tiles(int lx, int nz, int ny) {
   const int64_t rows = 3 * (int64_t)nz * ny;
-  if (plane_supported(lx, lx)) {   // plane kernels: at most one workgroup per plane
+  if (lx <= 64) {   // plane kernels: at most one workgroup per plane (a longer plane has more row tiles)
     switch (lx) {
 #define C(l)                                                                                 \
   case l: {                                                                                  \
     const int rp = cmin(Geo<float, l>::ROWP, Geo<double, l>::ROWP);                          \
     return std::max<int64_t>((rows + rp - 1) / rp, 3 * (int64_t)nz);                        \
   }
-      VIE_PLANE_CASES(C)
+      VIE_PLANE_SMALL(C)
 #undef C
     }
   }

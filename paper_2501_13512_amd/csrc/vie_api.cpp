@@ -511,7 +511,7 @@ MvmBatch<R> outer_batch(vie_problem& P, bool gated) {
   b.status = gated ? P.ostatus.as<int>() : nullptr;
   b.tw = tw_set<R>(P.ctx);
   b.zvariant = P.zvar[sizeof(R) == sizeof(float) ? 1 : 0];
-  b.plane = vie::plane_supported(b.lx, b.ly) ? 1 : 0;
+  b.plane = vie::plane_supported(b.lx, b.ly, (int)sizeof(R), 3 * (int64_t)b.nz * b.nsys) ? 1 : 0;
   b.pvariant = P.pvar[sizeof(R) == sizeof(float) ? 1 : 0];
   return b;
 }
@@ -537,7 +537,7 @@ MvmBatch<R> group_batch(vie_problem& P, Group& G, bool gated) {
   b.status = gated ? P.d_istatus.as<int>() + G.slot0 : nullptr;
   b.tw = tw_set<R>(P.ctx);
   b.zvariant = G.zvar[sizeof(R) == sizeof(float) ? 1 : 0];
-  b.plane = vie::plane_supported(b.lx, b.ly) ? 1 : 0;
+  b.plane = vie::plane_supported(b.lx, b.ly, (int)sizeof(R), 3 * (int64_t)b.nz * b.nsys) ? 1 : 0;
   b.pvariant = G.pvar[sizeof(R) == sizeof(float) ? 1 : 0];
   if (G.spec_tab.p)
     b.spec_tab = G.spec_tab.as<const cx<R>*>() + (sizeof(R) == sizeof(float) ? G.nsys : 0);
@@ -1861,7 +1861,9 @@ size_t plan_footprint(vie_context* ctx, const ProblemPlan& pl, bool all_spectra 
 int z_variant(int elem_bytes, const MvmBatch<double>& b) {
   return vie::zpass_rule(elem_bytes, b.lz, b.rooftop != 0, (int64_t)b.lx * b.ly * b.nsys);
 }
-int p_variant(const MvmBatch<double>& b) { return b.plane ? vie::plane_rule(b.lx, 3 * (int64_t)b.nz * b.nsys) : 0; }
+int p_variant(const MvmBatch<double>& b) {
+  return b.lx == b.ly && b.lx <= 64 ? vie::plane_rule(b.lx, 3 * (int64_t)b.nz * b.nsys) : 0;
+}
 
 void unpin_z(vie_problem& P) {
   const MvmBatch<double> b = outer_batch<double>(P, false);
