@@ -901,31 +901,47 @@ void mvm(const MvmBatch<R>& b, const c128* x, c128* y, bool mask_input, hipStrea
 
 // The z-pass variant of a shape; `cols` counts the columns of every system of
 // the batch.  Measured with the kernels alone, 5 us of event overhead with
-// them (f32 / f64, us; small: 1024 columns, large: 65536):
-//   length   32: V4 6.8 / 8.5 small; large V3 21.2 f32 (V4 24.0), V4 31.4 f64 (V3 34.9)
-//            36: V2 7.6, V4 7.2 / 8.1 small; large V3 35.4 / 46.9 (V2 45.6, V4 48.1)
-//            48: V0 7.8, V4 8.4 / 9.2 small; large V2 33.6 / 53.9 (V0 47.4 / 97.8)
-//            64: V4 7.8 / 8.4 small; large V4 34.8 / 51.3 (V3 38.2 / 66.9)
-//            72: V2 8.7, V0 8.5 / 8.5 small; large V2 57.8 (V4 59.6), V3 85.9 (V0 112.4)
-//            96: V0 9.0 / 10.3 small; large V2 64.4 (V0 71.7), V0 138.8 (V2 153.4)
-//           128: V4 10.5 / 10.5 small; large V4 81.1 / 169.4 (V2 96.2 / 203.3);
-//                rooftop f64 V3 27.1 (V4 34.8) from 9216 columns, 132.6 (V4 200.4) large
-//           144: V4 11.7 / 12.5 small; large V4 118.9 (V3 143.8), V3 271.7 (V4 299.2)
-//   from 192 on V4 (V0 equal, V2 and V3 slower); below 32 V0 and V4 are one.
-// The mirror columns (V1) were ahead in none of 96 shapes of lengths 4 to 256.
-// The lines between small and large lie where the two variants cross.
+// them (f32 / f64, us; small: 1024 columns, middle: 9216, large: 65536):
+//   length   32: V4 7.0 / 8.2 small; large V2 20.0 / 30.0 (V3 21.2 / 34.5, V4 23.2 / 32.1),
+//                rooftop V3 19.2 f32 (V2 19.4), V4 29.6 f64 (V2 29.7)
+//            36: f32 V2 7.8 small, 29.8 large (V3 35.8); f64 V4 7.7 small, V3 46.4 large (V2 49.7)
+//            48: V0 7.6, V4 8.7 small; middle V2 12.5 / 18.0 (V3 14.4 / 20.9), large V2 28.8 / 48.3
+//                (V3 37.3 / 72.6)
+//            64: V4 8.1 / 8.9 small; large V4 35.2 / 51.8 (V2 34.2 / 52.0)
+//            72: f32 V2 9.1 small, 45.7 large (V4 58.3); f64 V0 8.5 small, V2 18.6 middle (V3 22.5),
+//                75.6 large (V3 86.5), rooftop V3 75.5 (V2 79.1)
+//            96: V0 9.0 / 9.5 small; middle V2 18.6 / 22.1 (V0 20.3 / 24.4), large 63.4 / 124 (V0 74.8 / 139)
+//           128: V4 9.5 / 10.7 small; middle V2 18.1 / 25.4 (V4 20.0 / 28.4), large 74.3 / 153 (V4 79.7 / 172)
+//           144: f32 V4 11.5 small, 119 large (V2 120); f64 V2 12.0 small (V4 12.3), 204 large (V3 264)
+//           192: f32 V4 28.8 middle (V2 32.3); f64 V2 13.8 small, 38.9 middle (V4 53.3)
+//           256: f32 V4 34.9 middle (V2 34.7); f64 V2 14.3 small, 42.3 middle (V4 56.3)
+//   from 288 on V4 (f64 288: V4 33.8, V2 39.1 at 4096 columns; 512: V2 from 1.5 times as long)
+// Tiles of half a cache line (V2 of 72, 96 and f64 144, f32 128) rely on both
+// halves of a line meeting in the caches, so they end where the work buffer
+// leaves the Infinity Cache; 147456 / 262144 columns:
+//   f32  96: V2 159 / 336, V4 162 / 313;  f64  96: V2 304 / 677, V4 313 / 638
+//       128: V2 195 / 433, V4 183 / 363 (82944: 105, 103);  f64 72: V2 221 / 505, V3 232 / 463
+//   f64 144: V2 474 / 1035, V3 589 / 1118 (V4 652 / 1264)
+// Below 32 V0 and V4 are one.  The mirror columns (V1) were ahead in none of
+// 96 shapes of lengths 4 to 256.  The lines between small and large lie where
+// the two variants cross.
 int zpass_rule(int elem_bytes, int lz, bool rooftop, int64_t cols) {
   const bool f32 = elem_bytes == 4;
   if (lz < 32) return 0;
   switch (lz) {
-    case 32: return f32 && cols >= 32768 ? 3 : 4;
-    case 36: return f32 ? (cols >= 16384 ? 3 : 2) : (cols >= 32768 ? 3 : 4);
+    case 32:
+      if (cols < 32768) return 4;
+      return !rooftop ? 2 : (f32 ? 3 : 4);
+    case 36: return f32 ? 2 : (cols >= 32768 ? 3 : 4);
     case 48: return cols >= 8192 ? 2 : (f32 ? 0 : 4);
-    case 72: return f32 ? 2 : (cols >= 8192 ? 3 : 0);
-    case 96: return f32 && cols >= 16384 ? 2 : 0;
-    case 128: return !f32 && rooftop && cols >= 8192 ? 3 : 4;
-    case 144: return !f32 && cols >= 8192 ? 3 : 4;
-    default: return 4;
+    case 64: return 4;
+    case 72:
+      if (f32) return 2;
+      if (cols < 8192) return 0;
+      return cols >= (rooftop ? 32768 : 200000) ? 3 : 2;
+    case 96: return cols < 8192 ? 0 : (cols >= 200000 ? 4 : 2);
+    case 128: return cols < 8192 || (f32 && cols >= 80000) ? 4 : 2;
+    default: return f32 || lz >= 288 ? 4 : 2;
   }
 }
 

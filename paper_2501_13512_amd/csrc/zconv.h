@@ -42,34 +42,39 @@ __device__ __forceinline__ FoldCol fold_col(int f, int m, int L) {
 // per column and component, PF: spectrum values loaded into registers
 // before the data (their latency overlaps the forward transform).
 //   0: wide tiles (up to 1024 threads), max_butterflies threads per column
-//   2: wide tiles, min_butterflies rounded up to a power of two threads per
-//      column, prefetch (for L = 48: 4 threads, so a 16-column tile of the
-//      three components fills three whole wavefronts and each thread takes
-//      four radix-3 butterflies, where 3 threads leave a quarter of the
-//      third wavefront idle and take six butterflies, the last for one
-//      thread in three)
+//   2: one wavefront per component: 64 threads take the columns of half a
+//      cache line or more, with no more threads to a column than its first
+//      radix keeps busy.  The pass waits on memory, LDS and barriers in
+//      turn, so many small workgroups at different points of it hide more
+//      than few large ones (see zpass_rule for the times).
 //   3: one cache line of columns, min_butterflies threads, prefetch
 //   4: one cache line of columns, max_butterflies threads
-template <typename R, int LZ, int V>
+template <typename R, int LZ, int V, int K>
 struct ZColGeo {
   static constexpr int T = PlanInfo<LZ>::max_butterflies;
-  static constexpr int TB = V == 2 ? cmin(T, pow2_ceil(PlanInfo<LZ>::min_butterflies)) : PlanInfo<LZ>::min_butterflies;
+  static constexpr int TB = PlanInfo<LZ>::min_butterflies;
   static constexpr int ES = (int)sizeof(cx<R>);
   static constexpr int LDS_ZP = cmax(1, (144 * 1024) / (3 * LZ * ES));
   static constexpr int LINE = cmax(1, pow2_floor(cmin(LDS_ZP, 128 / ES)));
   static constexpr int WIDE = cmax(1, pow2_floor(cmin(LDS_ZP, cmin(64, cmax(128 / ES, 1024 / (3 * T))))));
-  static constexpr int ZP = (V == 3 || V == 4) ? LINE : WIDE;
-  static constexpr int TZ = (V == 2 || V == 3) ? cmin(TB, cmax(1, 1024 / (3 * ZP)))
-                                               : cmin(T, pow2_floor(cmax(1, 1024 / (3 * ZP))));
-  static constexpr bool PF = V == 2 || V == 3;
+  static constexpr int WAVE = cmin(64, cmax(64 / ES, 64 / pow2_ceil(TB)));
+  static constexpr int ZP = V == 2 ? WAVE : (V == 3 || V == 4) ? LINE : WIDE;
+  static constexpr int TZ = V == 2   ? cmin(T, 64 / ZP)
+                            : V == 3 ? cmin(TB, cmax(1, 1024 / (3 * ZP)))
+                                     : cmin(T, pow2_floor(cmax(1, 1024 / (3 * ZP))));
+  // the rooftop spectrum is three values a point instead of six: short
+  // columns have the registers for it (length 48 FP32, 65536 columns: 27.0 us
+  // with the prefetch, 28.7 without)
+  static constexpr bool PF = V == 3 || (V == 2 && K == 1 && LZ <= 48);
   // twiddles held in registers over both transforms: not in FP64 beside the
   // prefetched spectrum (64 systems of length 48: 49 us without, 60 with) or
   // for short columns
   static constexpr bool HOLD = sizeof(R) == 4 || (!PF && LZ >= 72);
   // wavefronts per SIMD that the registers must leave room for: FP64 beside
-  // the prefetched spectrum needs the third (64 systems of length 48: 48 us
-  // with three, 67 with the two that 170 registers allow)
+  // the prefetched spectrum needs the third (length 48, 65536 columns: 54 us
+  // with three, 70 with the two that 170 registers allow)
   static constexpr int WAVES = sizeof(R) == 8 && PF && LZ <= 64 ? 3 : 1;
+  static_assert(3 * LZ * ZP * ES <= 150 * 1024, "tile exceeds the LDS");
 };
 
 // Variant 1 (mirror columns): geometry.
@@ -179,9 +184,9 @@ __global__ void __launch_bounds__((3 * ZGeo<R, LZ>::T * ZGeo<R, LZ>::ZP)) k_zcon
 // the face gradient of cell values.  The spectrum buffer holds the octant of
 // G' followed by the full-length tables b_x[lx], b_y[ly], b_z[lz].
 template <typename R, int LZ, int V, int K>
-__global__ void __launch_bounds__((3 * ZColGeo<R, LZ, V>::TZ * ZColGeo<R, LZ, V>::ZP), (ZColGeo<R, LZ, V>::WAVES))
+__global__ void __launch_bounds__((3 * ZColGeo<R, LZ, V, K>::TZ * ZColGeo<R, LZ, V, K>::ZP), (ZColGeo<R, LZ, V, K>::WAVES))
     k_zconv_col(ZArgs<R> a) {
-  using G = ZColGeo<R, LZ, V>;
+  using G = ZColGeo<R, LZ, V, K>;
   constexpr int T = G::TZ, ZP = G::ZP;
   constexpr int NT = 3 * T * ZP;
   constexpr int HZ = LZ / 2;
@@ -348,15 +353,20 @@ __global__ void __launch_bounds__((3 * ZColGeo<R, LZ, V>::TZ * ZColGeo<R, LZ, V>
   fft_pencil<R, LZ, T, +1, true, false, PAD_OUT>(lds_ld, stg, slot, ZP, t, valid, tw);
 }
 
-template <typename R, int L, int V>
-static void launch_zcol(const ZArgs<R>& a, int nsys, hipStream_t s) {
-  using G = ZColGeo<R, L, V>;
+template <typename R, int L, int V, int K>
+static void launch_zcol_k(const ZArgs<R>& a, int nsys, hipStream_t s) {
+  using G = ZColGeo<R, L, V, K>;
   const int cols = a.ly * a.lx;
   const int blocks = ((cols + G::ZP - 1) / G::ZP) * nsys;
+  hipLaunchKernelGGL((k_zconv_col<R, L, V, K>), dim3(blocks), dim3(3 * G::TZ * G::ZP), 0, s, a);
+}
+
+template <typename R, int L, int V>
+static void launch_zcol(const ZArgs<R>& a, int nsys, hipStream_t s) {
   if (a.rooftop)
-    hipLaunchKernelGGL((k_zconv_col<R, L, V, 1>), dim3(blocks), dim3(3 * G::TZ * G::ZP), 0, s, a);
+    launch_zcol_k<R, L, V, 1>(a, nsys, s);
   else
-    hipLaunchKernelGGL((k_zconv_col<R, L, V, 0>), dim3(blocks), dim3(3 * G::TZ * G::ZP), 0, s, a);
+    launch_zcol_k<R, L, V, 0>(a, nsys, s);
 }
 
 template <typename R>
