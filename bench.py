@@ -140,7 +140,7 @@ def group_traffic(dom_z, workload, precision, s_el):
              and e.get("precision") == precision and e.get("lz") == lz and e.get("source_hash") == h]
     if not cands:
         return None
-    e = max(cands, key=lambda c: c["dispatches"])   # the group's tuned variant runs most
+    e = max(cands, key=lambda c: c["dispatches"])   # the group's own variant runs most
     full = dom_z["systems"] * 2 * 3 * bz * ly * lx * s_el + 6 * (lx // 2 + 1) * (ly // 2 + 1) * (lz // 2 + 1) * s_el
     return e["bytes_per_launch"] * dom_z["bytes_per_launch"] / full
 

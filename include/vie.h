@@ -391,7 +391,7 @@ vie_status vie_far_field(vie_problem* p, const void* pol_dev, int32_t n_dir, con
  *   pol_dev:  3*nvox complex, the solution P (device);
  *   rhat_dev: n_dir unit directions, 3 doubles each (device; not checked);
  *   f_dev:    3*n_dir complex written (device), as vie_far_field's f_out.
- * The per-chunk partial sums live in a fixed array of 8 MiB that the library
+ * The phase tables and partial sums live in a fixed array of 8 MiB that the library
  * keeps on every GPU it runs on until the process ends (its device address
  * is looked up by vie_context_create).  Every call on a GPU shares that
  * GPU's array: calls that overlap on one GPU race, so run them in order (one
@@ -447,7 +447,7 @@ vie_status vie_solve_batch(vie_problem* p, int32_t nrhs, const void* e_inc_dev, 
  * own problem's spectra, all on the batched kernels (no one-workgroup block
  * solver); a problem that has stopped contributes zero right-hand sides.
  * The outer products use the kernel variants of problems[0] (pinned or
- * tuned).  The FP64 true residual, mixed-mode refinement and the fields are
+ * by shape).  The FP64 true residual, mixed-mode refinement and the fields are
  * then formed per problem as in vie_solve_device.  inner_iters_total and
  * precond_applies are the batch's totals.  FGMRES and CGS, and n = 1, solve
  * the problems one after another.  Batch storage (1/chi, 12 vectors and a
@@ -465,9 +465,9 @@ vie_status vie_solve_many(int32_t n, vie_problem* const* problems, const void* c
  * partition and options) are admitted in arrival order as solver slots and
  * device memory free up, and run concurrently, each slot on its own HIP
  * stream, each request in a problem of its own (created when admitted,
- * destroyed when it finishes).  Green spectra and tuned kernel choices are
- * cached in the context and shared by requests of the same shapes, so a
- * request gives the same result alone or among others.  Results come back
+ * destroyed when it finishes).  Green spectra are cached in the
+ * context and shared by requests of the same shapes, and the kernels are
+ * chosen by shape, so a request gives the same result alone or among others.  Results come back
  * to host memory.
  *
  * Memory admission: a request is started only when the context's memory in
