@@ -110,10 +110,11 @@ void mvm_pass5(const MvmBatch<R>& b, const KBatch* k, const FuseArgs& f, const c
 constexpr int kZPassVariants = 5;
 int zpass_rule(int elem_bytes, int lz, bool rooftop, int64_t cols);
 
-// The plane-kernel variant (planes per workgroup: 0 as LDS allows, 1 two,
-// 2 one) of an unpinned batch: transform length, planes of all systems.
+// The plane-kernel variant (planes per workgroup: 0 as LDS allows, 1 two or
+// one by 512 threads, 2 one) of an unpinned batch: transform length, planes of
+// all systems, most planes of the batches that share the choice.
 constexpr int kPlaneVariants = 3;
-int plane_rule(int l, int64_t planes);
+int plane_rule(int l, int64_t planes, int64_t most);
 
 // Chunks per system of the fused first/last passes (for partial sizing).
 int64_t mvm_row_tiles(int lx, int nz, int ny);

@@ -295,7 +295,7 @@ __global__ void __launch_bounds__((Geo<R, L>::T * Geo<R, L>::ROWP)) k_row_inv_lo
 // A workgroup takes NPL consecutive planes (c, z) of one system; LDS holds
 // them as [NPL][L][L + 1] (rows padded against bank conflicts on columns).
 // Variant PV sets NPL: 0 as many planes as 48 KB of LDS hold (at most 16),
-// 1 at most two, 2 one plane.  From 96 on a workgroup is 1024 threads and one
+// 1 at most two (from 48 on one plane with twice the threads), 2 one plane.  From 96 on a workgroup is 1024 threads and one
 // plane, the CU's LDS holding no second FP64 one.  Fewer planes per workgroup mean more, shorter
 // workgroups: the product's latency falls when few systems are active (two
 // 32 x 32 planes of a 16 x 16 box take 3 transform rounds of 32 pencils
@@ -306,10 +306,17 @@ struct PlaneGeo {
   static constexpr int LP = L + 1;
   static constexpr bool FITS = L * LP * ES <= 150 * 1024;
   static constexpr int NPL_LDS = cmax(1, cmin(16, (48 * 1024) / (L * LP * ES)));
-  static constexpr int NPL = PV == 0 ? NPL_LDS : (PV == 1 ? cmin(2, NPL_LDS) : 1);
-  static constexpr int BT = L > 64 ? 1024 : 256;
+  static constexpr int NPL = PV == 0 ? NPL_LDS : (PV == 1 && L < 48 ? cmin(2, NPL_LDS) : 1);
+  static constexpr int BT = L > 64 ? 1024 : (PV == 1 && L >= 48 ? 512 : 256);
   static constexpr int T = PlanInfo<L>::max_butterflies;
   static constexpr int PP = BT / T;
+  // where 256 threads take all rows at once, pencils go to sets of 256 in
+  // turn: the row phase then leaves whole wavefronts idle, not half the lanes
+  // of each
+  static constexpr int SET = L / 2 * T <= 256 ? cmin(BT, 256) : BT;
+  static constexpr int SP = SET / T;
+  static __device__ __forceinline__ int pencil() { return threadIdx.x % SP + threadIdx.x / SET * SP; }
+  static __device__ __forceinline__ int place() { return threadIdx.x % SET / SP; }
   static_assert(BT % T == 0, "pencil threads must divide the workgroup");
 };
 
@@ -329,7 +336,7 @@ __global__ void __launch_bounds__((PlaneGeo<R, L, PV>::BT)) k_plane_fwd(RowArgs<
   const int64_t v0 = sys * a.vstride + (int64_t)pl0 * pe;
   const int mode = a.in_mode;
   double acc = 0.0;
-  const TwRegs<R, L, T> tw(a.tw, threadIdx.x / PP);
+  const TwRegs<R, L, T> tw(a.tw, G::place());
   // zero the padding columns that the transform reads, [nx, L/2), of rows y < ny
   const int padw = half_padded(L) - nx;
   for (int e = threadIdx.x; e < npl * ny * padw; e += BT) {
@@ -418,7 +425,7 @@ __global__ void __launch_bounds__((PlaneGeo<R, L, PV>::BT)) k_plane_fwd(RowArgs<
   // that a stage with fewer butterflies leaves idle form whole wavefronts,
   // which skip it; the row stride LP keeps the lanes' LDS banks distinct.
   {
-    const int p = threadIdx.x % PP, t = threadIdx.x / PP;
+    const int p = G::pencil(), t = G::place();
     const int nrows = npl * ny;
     for (int r0 = 0; r0 < nrows; r0 += PP) {
       const int row = r0 + p;
@@ -433,7 +440,7 @@ __global__ void __launch_bounds__((PlaneGeo<R, L, PV>::BT)) k_plane_fwd(RowArgs<
   }
   // y transforms of the L columns (rows >= ny are zero), out to HBM
   {
-    const int p = threadIdx.x % PP, t = threadIdx.x / PP;
+    const int p = G::pencil(), t = G::place();
     const int ncols = npl * L;
     cx<R>* w = a.work + sys * a.wstride + (int64_t)pl0 * L * L;
     for (int c0 = 0; c0 < ncols; c0 += PP) {
@@ -486,11 +493,11 @@ __global__ void __launch_bounds__((PlaneGeo<R, L, PV>::BT)) k_plane_inv_local(Ro
       }
     }
   };
-  const TwRegs<R, L, T> tw(a.tw, threadIdx.x / PP);
+  const TwRegs<R, L, T> tw(a.tw, G::place());
   load(0);   // in flight during the transforms
   // y inverse of the L columns from HBM, rows k < ny kept in LDS
   {
-    const int p = threadIdx.x % PP, t = threadIdx.x / PP;
+    const int p = G::pencil(), t = G::place();
     const int ncols = npl * L;
     const cx<R>* w = a.work + sys * a.wstride + (int64_t)pl0 * L * L;
     for (int c0 = 0; c0 < ncols; c0 += PP) {
@@ -510,7 +517,7 @@ __global__ void __launch_bounds__((PlaneGeo<R, L, PV>::BT)) k_plane_inv_local(Ro
   // x inverse of the rows y < ny, in place, cropped to nx (lanes over rows
   // as in the forward kernel)
   {
-    const int p = threadIdx.x % PP, t = threadIdx.x / PP;
+    const int p = G::pencil(), t = G::place();
     const int nrows = npl * ny;
     for (int r0 = 0; r0 < nrows; r0 += PP) {
       const int row = r0 + p;
@@ -952,12 +959,21 @@ int zpass_rule(int elem_bytes, int lz, bool rooftop, int64_t cols) {
 //   length 16: 384 planes 15.4, 13.6, 14.6 / 15.9, 14.7, 15.7; 6144: 21.2, 28.1, 41.7 / 25.1, 36.8, 59.6
 //          24: 576: 29.4, 16.8, 15.5 / 21.9, 18.6, 17.5; 9216: 59.0, 44.7, 52.5 / 60.5, 54.1, 63.7
 //          32: 768: 25.6, 18.2, 17.6 / 21.3, 21.1, 19.9; 12288: 84.4, 61.5, 69.1 / 100.6, 100.1, 103.3
-//          48: 768: 35.1, 35.0, 26.1 / 29.9, 29.7, 29.5; 3072: 63.8, 63.0, 56.9; 64: one plane in all
-int plane_rule(int l, int64_t planes) {
+//          48: 768: 35.1, 35.0, 26.1 / 29.9, 29.7, 29.5; 3072: 63.8, 63.0, 56.9
+// From 48 on variant 1 is one plane by 512 threads; products of 24x24xnz and
+// 32x32xnz with variants 1, 2:
+//          48 f32: nz 2 14.3, 17.5; 64 20.9, 24.1; 128 29.2, 31.2; 256 56.3, 52.6
+//             f64: nz 2 14.6, 18.3; 64 26.2, 29.8; 128 39.2, 38.8; 256 68.7, 63.0
+//          64 f32: nz 2 12.5, 15.3; 64 22.2, 24.4; 128 32.2, 33.1; 256 57.5, 55.2
+//             f64: nz 2 13.9, 16.2; 64 28.8, 30.6; 96 39.0, 37.7; 256 90.4, 87.1
+// `most` is the plane count of the batches that share the choice: a problem's
+// own product runs in batches of several right-hand sides too, whose sums
+// must be those of one alone.
+int plane_rule(int l, int64_t planes, int64_t most) {
   if (l <= 8) return 0;
   if (l <= 16) return planes > 2048 ? 0 : 1;
   if (l <= 32) return planes > 1024 ? 1 : 2;
-  return 2;
+  return most <= 192 ? 1 : 2;
 }
 
 #define VIE_MVM_INST(R)                                                                                           \

@@ -1861,8 +1861,11 @@ size_t plan_footprint(vie_context* ctx, const ProblemPlan& pl, bool all_spectra 
 int z_variant(int elem_bytes, const MvmBatch<double>& b) {
   return vie::zpass_rule(elem_bytes, b.lz, b.rooftop != 0, (int64_t)b.lx * b.ly * b.nsys);
 }
-int p_variant(const MvmBatch<double>& b) {
-  return b.lx == b.ly && b.lx <= 64 ? vie::plane_rule(b.lx, 3 * (int64_t)b.nz * b.nsys) : 0;
+// sharing: right-hand sides that the batches of the same choice are taken to have
+constexpr int kSharedRhs = 8;
+int p_variant(const MvmBatch<double>& b, int64_t sharing) {
+  const int64_t planes = 3 * (int64_t)b.nz * b.nsys;
+  return b.lx == b.ly && b.lx <= 64 ? vie::plane_rule(b.lx, planes, planes * sharing) : 0;
 }
 
 void unpin_z(vie_problem& P) {
@@ -1875,8 +1878,8 @@ void unpin_z(vie_problem& P, Group& G) {
   G.zvar[0] = z_variant(8, b);
   G.zvar[1] = z_variant(4, b);
 }
-void unpin_p(vie_problem& P) { P.pvar[0] = P.pvar[1] = p_variant(outer_batch<double>(P, false)); }
-void unpin_p(vie_problem& P, Group& G) { G.pvar[0] = G.pvar[1] = p_variant(group_batch<double>(P, G, false)); }
+void unpin_p(vie_problem& P) { P.pvar[0] = P.pvar[1] = p_variant(outer_batch<double>(P, false), kSharedRhs); }
+void unpin_p(vie_problem& P, Group& G) { G.pvar[0] = G.pvar[1] = p_variant(group_batch<double>(P, G, false), 1); }
 
 // inner_only: the blocks and their inner solves only (no full-grid operator:
 // no outer spectra, work buffer or Krylov vectors); used for the stacked
@@ -2443,8 +2446,8 @@ vie_status vie_problem_set_plane(vie_problem* p, int32_t precision, int32_t vari
         x->pvar[q] = variant;
         for (auto& G : x->groups) G.pvar[q] = variant;
       } else {
-        if (x->spec) x->pvar[q] = p_variant(outer_batch<double>(*x, false));
-        for (auto& G : x->groups) G.pvar[q] = p_variant(group_batch<double>(*x, G, false));
+        if (x->spec) x->pvar[q] = p_variant(outer_batch<double>(*x, false), kSharedRhs);
+        for (auto& G : x->groups) G.pvar[q] = p_variant(group_batch<double>(*x, G, false), 1);
       }
       // captured inner steps hold the old kernels
       ApiShared api;

@@ -66,3 +66,29 @@ def test_solve(vie_ctx, shape):
             assert float(res) <= 10 * tol, (prec, float(res))
         finally:
             P.close()
+
+
+@pytest.mark.parametrize("prec", [V.VIE_FP64, V.VIE_MIXED])
+@pytest.mark.parametrize("shape", [(24, 19, 1), (19, 24, 5), (32, 25, 3), (25, 32, 11)])
+def test_plane_by_512_threads(vie_ctx, shape, prec):
+    """Variant 1 of lengths 48 and 64 gives the bits of the 256-thread plane."""
+    case = W.random_tiny(sum(s * 43 ** i for i, s in enumerate(shape)), shape, fill=0.7)
+    g = op.Grid.from_case(case)
+    rng = np.random.default_rng(9)
+    x = rng.standard_normal((3,) + case.shape) + 1j * rng.standard_normal((3,) + case.shape)
+    P = V.Problem(V.make_grid(case.nx, case.ny, case.nz, case.dx, case.dy, case.dz, case.wavelength), case.eps, None, 0,
+                  ctx=vie_ctx)
+    got = {}
+    try:
+        xd = torch.from_numpy(x).cuda()
+        for variant in (1, 2):
+            V.vie_problem_set_plane(P.handle, prec, variant)
+            yd = torch.full_like(xd, complex("nan"))
+            V.vie_matvec(P.handle, prec, xd, yd)
+            torch.cuda.synchronize()
+            got[variant] = yd.cpu().numpy()
+    finally:
+        P.close()
+    assert np.array_equal(got[1], got[2])
+    want = op.matvec_fft(g, x * g.mask)
+    assert np.abs(got[1] - want).max() / np.abs(want).max() <= TOL[prec]
