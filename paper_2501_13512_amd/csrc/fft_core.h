@@ -256,6 +256,15 @@ __device__ __forceinline__ cx<R> twiddled(cx<R> v, cx<R> w) {
 enum Pad { PAD_NONE = 0, PAD_IN = 1, PAD_OUT = 2 };
 // elements of a padded pencil that can be voxels
 __host__ __device__ constexpr int half_padded(int l) { return l % 2 == 0 ? l / 2 : (l + 1) / 2; }
+// PadIn: whether the first stage of a PAD_IN transform leaves out its upper
+// inputs, and the elements [0, reads) that it asks its loader for.  Length 3
+// has no even first radix: it reads all three, of which two can be voxels.
+template <int L>
+struct PadIn {
+  static constexpr bool half = L % 2 == 0 && RadInfo<typename Plan<L>::type>::first % 2 == 0;
+  static constexpr int reads = half ? L / 2 : L;
+  static_assert(reads >= half_padded(L), "a voxel would not be read");
+};
 
 // Place of element i of a pencil in its LDS slot: consecutive elements LS
 // apart, or, for pencils that lie along their lanes (rows), one element left
@@ -285,7 +294,7 @@ __device__ __forceinline__ void fft_stage(Load& ld, Store& st, cx<R>* lds, Slot 
   constexpr int NPT = (NB + T - 1) / T;
   constexpr bool READS_SLOT = !FIRST || LDLDS;
   constexpr bool WRITES_SLOT = !LAST || STLDS;
-  constexpr bool HIN = FIRST && PAD == PAD_IN && L % 2 == 0 && RAD % 2 == 0;
+  constexpr bool HIN = FIRST && PAD == PAD_IN && PadIn<L>::half;
   // the last stage's outputs b + m P, b < P: none of m from here on is kept
   // (radix 16 forms them all: it would spare a ninth of its additions)
   constexpr int MOUT = LAST && PAD == PAD_OUT && L % 2 == 0 && RAD <= 8 ? (RAD + 1) / 2 : RAD;
@@ -342,8 +351,8 @@ __device__ __forceinline__ void fft_stages(Load& ld, Store& st, cx<R>* lds, Slot
 // Transform one pencil of length L: x_n = ld(n) (n < L) -> st(k, X_k).
 // Threads t in [0, T) of the pencil take part; tvalid = false threads still
 // hit the barriers but touch no data.  The pencil's LDS slot is the exchange
-// buffer between stages; see fft_stage for LDLDS / STLDS.  With PAD_IN (even
-// L) ld is not asked for n >= L/2; with PAD_OUT st may not be given k >= L/2.
+// buffer between stages; see fft_stage for LDLDS / STLDS.  With PAD_IN ld is
+// asked for n < PadIn<L>::reads; with PAD_OUT st may not be given k >= L/2.
 template <typename R, int L, int T, int DIR, bool LDLDS = false, bool STLDS = false, int PAD = PAD_NONE, class Load,
           class Store, class Slot, bool HOLD>
 __device__ __forceinline__ void fft_pencil(Load ld, Store st, cx<R>* lds, Slot ls, int t, bool tvalid,

@@ -143,7 +143,7 @@ __global__ void __launch_bounds__((Geo<R, L>::T * Geo<R, L>::ROWP)) k_row_fwd(Ro
   const KState& ks = a.k.st[sys];
   const bool first = mode == 1 && ks.iters == 0;
   double acc = 0.0;
-  constexpr int LH = half_padded(L);     // elements that the transform reads
+  constexpr int LH = PadIn<L>::reads;   // elements that the transform reads
   constexpr int E = (LH + T - 1) / T;   // per thread
   constexpr int CH = 4;                // elements per load batch
   c128 rv[CH], pv[CH], vv[CH];
@@ -337,8 +337,8 @@ __global__ void __launch_bounds__((PlaneGeo<R, L, PV>::BT)) k_plane_fwd(RowArgs<
   const int mode = a.in_mode;
   double acc = 0.0;
   const TwRegs<R, L, T> tw(a.tw, G::place());
-  // zero the padding columns that the transform reads, [nx, L/2), of rows y < ny
-  const int padw = half_padded(L) - nx;
+  // zero the padding columns that the transform reads, of rows y < ny
+  const int padw = PadIn<L>::reads - nx;
   for (int e = threadIdx.x; e < npl * ny * padw; e += BT) {
     const int row = e / padw, xx = nx + (e - row * padw);
     const int q = (int)udiv_m((unsigned)row, a.m_ny);
