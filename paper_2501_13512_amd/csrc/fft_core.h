@@ -120,7 +120,12 @@ __host__ __device__ __forceinline__ void dft(cx<R>* v) {
         t = rot_q<DIR>(o[4]);
       } else {
         const R wr = cr[k], wi = sg * ci[k];
-        t = mk<R>(o[k].x * wr - o[k].y * wi, o[k].x * wi + o[k].y * wr);
+        if (k == 2 && DIR < 0)
+          // wi = -wr: which of the two products is fused would be the compiler's
+          // choice, which differs with the code around (length 256 in FP32)
+          t = mk<R>(fma1(-o[k].y, wi, o[k].x * wr), fma1(o[k].y, wr, o[k].x * wi));
+        else
+          t = mk<R>(o[k].x * wr - o[k].y * wi, o[k].x * wi + o[k].y * wr);
       }
       v[k] = e[k] + t;
       v[k + 8] = e[k] - t;
