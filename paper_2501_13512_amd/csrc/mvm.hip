@@ -41,6 +41,13 @@ struct Geo {
   static constexpr int ES = (int)sizeof(cx<R>);
   // rows (contiguous pencils): ~256 threads, LDS [ROWP][L]
   static constexpr int ROWP = cmax(1, cmin(256 / T, (64 * 1024) / (L * ES)));
+  // twiddles held over a row (column) transform: not where their registers cost
+  // a wavefront or more (rows of 192x40x96, FP32: 22.6 us without, 30.7 with;
+  // columns of 40x192x96: 29.3, 35.3; FP64 columns of 40x72x96: 24.9, 26.6)
+  static constexpr bool HOLD = sizeof(R) == 8 || L != 384;
+  static constexpr bool HOLD_COL = HOLD && L != 144;
+  // pass 5 asks for its vectors before the transform
+  static constexpr bool EARLY = HOLD && (sizeof(R) == 4 || L < 72 || L == 256);
   static constexpr int RAD0 = RadInfo<typename Plan<L>::type>::first;
   using RS = RowSlot<RAD0>;                                  // rows with gaps against bank conflicts
   static constexpr int ROWL = RAD0 > 1 ? L + L / RAD0 : L;
@@ -112,7 +119,7 @@ __global__ void __launch_bounds__((Geo<R, L>::T * Geo<R, L>::ROWP)) k_row_fwd(Ro
   cx<R>* slot = lds + p * G::ROWL;
   const int nx = a.nx;
   const int mode = a.in_mode;
-  const TwRegs<R, L, T> tw(a.tw, t);
+  const TwRegs<R, L, T, G::HOLD> tw(a.tw, t);
   auto st = [&](int k, cx<R> v) { w[k] = v; };
   if (mode == 0) {
     // nothing in the loaders uses a loaded value under its bounds check, so a
@@ -244,8 +251,8 @@ __global__ void __launch_bounds__((Geo<R, L>::T * Geo<R, L>::ROWP)) k_row_inv_lo
       }
     }
   };
-  const TwRegs<R, L, T> tw(a.tw, t);
-  constexpr bool EARLY = E <= 2 * CH;   // the operands in flight during the transform, where it holds few values
+  const TwRegs<R, L, T, G::HOLD> tw(a.tw, t);
+  constexpr bool EARLY = G::EARLY && E <= 2 * CH;   // the operands in flight during the transform, where it holds few values
   if (EARLY) load(0);
   fft_pencil<R, L, T, +1, false, true, PAD_OUT>(ld, sts, slot, RS(), t, valid, tw);
 
@@ -621,7 +628,7 @@ __global__ void __launch_bounds__((Geo<R, L>::TC * Geo<R, L>::COLP)) k_col(ColAr
   auto st = [&](int k, cx<R> v) {
     if (k < n_out) base[(int64_t)k * inner] = v;
   };
-  const TwRegs<R, L, G::TC> tw(a.tw, t);
+  const TwRegs<R, L, G::TC, G::HOLD_COL> tw(a.tw, t);
   fft_pencil<R, L, G::TC, DIR, false, false, PAD>(ld, st, lds + p, G::COLP, t, valid, tw);
 }
 
