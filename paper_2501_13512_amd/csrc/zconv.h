@@ -58,18 +58,23 @@ struct ZColGeo {
   static constexpr int LINE = cmax(1, pow2_floor(cmin(LDS_ZP, 128 / ES)));
   static constexpr int WIDE = cmax(1, pow2_floor(cmin(LDS_ZP, cmin(64, cmax(128 / ES, 1024 / (3 * T))))));
   static constexpr int WAVE = cmin(64, cmax(64 / ES, 64 / pow2_ceil(TB)));
-  static constexpr int ZP = V == 2 ? WAVE : (V == 3 || V == 4) ? LINE : WIDE;
-  static constexpr int TZ = V == 2   ? cmin(T, 64 / ZP)
+  // FP32 144 takes V2's place for many columns: one cache line of columns by 16
+  // threads each, with the prefetch (196608 columns: V4 329 us, half a line by
+  // one wavefront per component 360)
+  static constexpr bool LINE2 = V == 2 && sizeof(R) == 4 && LZ == 144;
+  static constexpr int ZP = V == 2 && !LINE2 ? WAVE : (V == 0 ? WIDE : LINE);
+  static constexpr int TZ = LINE2    ? pow2_ceil(TB)
+                            : V == 2 ? cmin(T, 64 / ZP)
                             : V == 3 ? cmin(TB, cmax(1, 1024 / (3 * ZP)))
                                      : cmin(T, pow2_floor(cmax(1, 1024 / (3 * ZP))));
   // the rooftop spectrum is three values a point instead of six: short
   // columns have the registers for it (length 48 FP32, 65536 columns: 27.0 us
   // with the prefetch, 28.7 without)
-  static constexpr bool PF = V == 3 || (V == 2 && K == 1 && LZ <= 48);
+  static constexpr bool PF = V == 3 || LINE2 || (V == 2 && K == 1 && LZ <= 48);
   // twiddles held in registers over both transforms: not in FP64 beside the
   // prefetched spectrum (64 systems of length 48: 49 us without, 60 with) or
   // for short columns
-  static constexpr bool HOLD = sizeof(R) == 4 || (!PF && LZ >= 72);
+  static constexpr bool HOLD = !LINE2 && (sizeof(R) == 4 || (!PF && LZ >= 72));
   // wavefronts per SIMD that the registers must leave room for: FP64 beside
   // the prefetched spectrum needs the third (length 48, 65536 columns: 54 us
   // with three, 70 with the two that 170 registers allow)
@@ -367,6 +372,15 @@ static void launch_zcol(const ZArgs<R>& a, int nsys, hipStream_t s) {
     launch_zcol_k<R, L, V, 1>(a, nsys, s);
   else
     launch_zcol_k<R, L, V, 0>(a, nsys, s);
+}
+
+// The kernel of a column-set variant: below 32 all are variant 0; where no
+// column count is better off with variants 2 and 3 (from 288 on, and 2 at 192
+// in FP32) they are variant 4, which also keeps the variants of a length equal
+// bit for bit.
+template <typename R>
+constexpr int zcol_kernel(int l, int v) {
+  return l < 32 ? 0 : (l >= 288 || (l == 192 && v == 2 && sizeof(R) == 4)) ? 4 : v;
 }
 
 template <typename R>
