@@ -397,11 +397,11 @@ void launch_zconv(int L, const ZArgs<R>& a, int nsys, hipStream_t s) {
     } else if (l < 32 || a.variant == 0) {                                                        \
       launch_zcol<R, l, 0>(a, nsys, s);                                                           \
     } else if (a.variant == 2) {                                                                  \
-      launch_zcol<R, l, (l < 32 ? 0 : 2)>(a, nsys, s);                                            \
+      launch_zcol<R, l, zcol_kernel<R>(l, 2)>(a, nsys, s);                                        \
     } else if (a.variant == 3) {                                                                  \
-      launch_zcol<R, l, (l < 32 ? 0 : 3)>(a, nsys, s);                                            \
+      launch_zcol<R, l, zcol_kernel<R>(l, 3)>(a, nsys, s);                                        \
     } else {                                                                                      \
-      launch_zcol<R, l, (l < 32 ? 0 : 4)>(a, nsys, s);                                            \
+      launch_zcol<R, l, zcol_kernel<R>(l, 4)>(a, nsys, s);                                        \
     }                                                                                             \
     break;                                                                                        \
   }
