@@ -692,18 +692,28 @@ static void launch_col(int L, const ColArgs<R>& a, hipStream_t s) {
 #define VIE_PLANE_CASES(F) VIE_PLANE_SMALL(F) F(96) F(128)
 
 // Whether a batch's x and y transforms run per plane; `planes` as for
-// plane_rule.  Up to 64 always.  A plane of length 96 or 128 takes most of a
-// CU's LDS and 8 to 10 us of its time, so few planes are better spread over
-// the chip as rows and columns: product of 48x48xnz / 64x64xnz, rows and
-// columns against planes, us:
-//   96 f32: nz 16 24.6, 27.3; 32 33.0, 32.3; 48 44.6, 41.1; 64 49.3, 41.1; 128 74.6, 74.7; 256 146, 150
-//      f64: nz 16 31.5, 35.2; 32 42.5, 41.6; 48 54.1, 49.0; 64 61.0, 54.8; 128 108, 108; 256 210, 203
-//  128 f32: nz 16 30.4, 31.1; 32 41.5, 33.9; 48 52.9, 42.7; 64 55.1, 46.2; 128 101, 94; 256 231, 214
-// FP64 planes of length 128 exceed the LDS.
+// plane_rule.  Up to 64 always.  A plane of length 96 or 128 takes a CU to
+// itself and 8 to 10 us of its time, so few planes are better spread over the
+// chip as rows and columns, and so is a round of the 256 CUs that is far from
+// full.  Product of 48x48xnz / 64x64xnz, rows and columns against planes, us:
+//   96 f32:  93 planes 33.0, 33.4; 96 33.3, 32.1; 144 42.6, 39.3; 255 57.8, 51.9; 258 60.0, 67.3;
+//            384 73.3, 74.9; 510 110, 111; 768 146, 146
+//      f64:  96 42.0, 41.6; 144 52.3, 47.1; 255 77.6, 69.0; 258 78.6, 86.8; 384 94.5, 94.1 (40x40: 90.1, 91.6);
+//            432 134, 132; 510 149, 142; 516 148, 159; 600 185, 188; 660 194, 194; 768 210, 204
+//  128 f32:  96 41.1, 34.2; 255 74.7, 67.2; 258 78.3, 83.2; 285 82.3, 84.0; 300 89.9, 89.8 (52x52: 83.2, 85.3);
+//            330 93.4, 92.1; 384 99.5, 93.8; 516 157, 158; 768 233, 215
+// FP64 planes of length 128 exceed the LDS.  The choice follows the planes of
+// one right-hand side (a batch's sums must be those of one alone), so batches
+// that fill a little more than a round lose up to 9%: 3 x 48x48x32, 2 x 48x48x48.
 bool plane_supported(int lx, int ly, int elem_bytes, int64_t planes) {
   if (lx != ly || lx > 128) return false;
-  if (lx > 64 && (planes < 96 || (lx == 128 && elem_bytes == 8) || (lx == 96 && elem_bytes == 4 && planes > 384)))
-    return false;
+  if (lx > 64) {
+    const bool f32 = elem_bytes == 4;
+    const int64_t last = (planes - 1) % 256 + 1;   // planes of the last round
+    if (planes < 96) return false;
+    if (lx == 96 && planes > 256 && (f32 || last < 154)) return false;
+    if (lx == 128 && (!f32 || (planes > 256 && planes < 320))) return false;
+  }
 #define C(l) \
   if (lx == l) return true;
   VIE_PLANE_CASES(C)
