@@ -15,6 +15,11 @@
 // the product is real: [u.re, -w.im] and [u.im, w.re] times [cos a; sin a],
 // half the operations of the complex one.  It runs on the FP64 matrix
 // instructions; cos and sin come from a table per (x, direction).
+//
+// Few directions, small grids and boxes of one voxel in x leave that product
+// mostly padding (192 directions and four pairs of x at a time, three kernels):
+// they are summed directly, a sine and cosine per voxel and direction
+// (FarShape has the line and both sides).
 #include <algorithm>
 #include <stdexcept>
 #include <string>
@@ -29,7 +34,8 @@ constexpr int FF_J = 32;           // mirror pairs of x per workgroup
 constexpr int FF_NT = 3;           // 16-direction tiles per wavefront
 constexpr int FF_DIRS = 4 * FF_NT * 16;   // directions per workgroup
 constexpr int FF_LD = 2 * FF_J + 4;       // LDS row of a staged pencil: rows start 8 banks apart
-constexpr int FF_PARTS = 512;             // workgroups per direction block
+constexpr int FF_PARTS = 512;             // workgroups per direction block, about
+constexpr int FF_CHUNK = 2048;            // voxels per workgroup of the direct sum
 
 // Tables and partial sums of the far field that allocates nothing: a fixed
 // array of 8 MiB on every GPU the library runs on, held until the process
@@ -72,7 +78,7 @@ __global__ void __launch_bounds__(FF_T) k_far_table(const double* rhat, int ndir
 // are staged in LDS (real and imaginary result rows as separate row tiles, so
 // a lane ends up with both parts of its rows); a wavefront multiplies all six
 // row tiles with its 48 directions, applies the phase of (y, z) and adds its
-// rows up.  A grid has at most FF_PARTS workgroups per direction block (two
+// rows up.  A grid has about FF_PARTS workgroups per direction block (two
 // for each compute unit), which bounds the partial sums as well.  Bound by
 // the FP64 matrix rate: 128 x 128 x 32 cells and 181 directions take 1.2
 // GFLOP, 15 us at that rate; measured 31 us (wavefronts of a workgroup load and
@@ -178,8 +184,39 @@ __global__ void __launch_bounds__(FF_T, 2) k_far_partial(const c128* P, int nx, 
   }
 }
 
+// The direct sum of one chunk of voxels for one direction.
+__global__ void __launch_bounds__(FF_T) k_far_direct(const c128* P, int nx, int ny, int nz, double dx, double dy,
+                                                     double dz, double k0, const double* rhat, int nchunk,
+                                                     double* part) {
+  const int dir = blockIdx.x / nchunk, chunk = blockIdx.x - dir * nchunk;
+  const double rx = rhat[3 * dir], ry = rhat[3 * dir + 1], rz = rhat[3 * dir + 2];
+  const int64_t nv = (int64_t)nx * ny * nz, xy = (int64_t)nx * ny, v0 = (int64_t)chunk * FF_CHUNK;
+  const double cx0 = 0.5 * (nx - 1), cy0 = 0.5 * (ny - 1), cz0 = 0.5 * (nz - 1);
+  double acc[6] = {0, 0, 0, 0, 0, 0};
+  for (int64_t v = v0 + threadIdx.x; v < v0 + FF_CHUNK && v < nv; v += FF_T) {
+    const int z = (int)(v / xy);
+    const int64_t r = v - (int64_t)z * xy;
+    const int y = (int)(r / nx), x = (int)(r - (int64_t)y * nx);
+    double s, c;
+    sincos(k0 * (rx * ((x - cx0) * dx) + ry * ((y - cy0) * dy) + rz * ((z - cz0) * dz)), &s, &c);
+#pragma unroll
+    for (int q = 0; q < 3; ++q) {
+      const c128 p = P[q * nv + v];
+      acc[2 * q] += p.x * c - p.y * s;
+      acc[2 * q + 1] += p.x * s + p.y * c;
+    }
+  }
+  block_sum<6>(acc);
+  if (threadIdx.x == 0) {
+    double* o = part + ((int64_t)dir * nchunk + chunk) * 6;
+#pragma unroll
+    for (int k = 0; k < 6; ++k) o[k] = acc[k];
+  }
+}
+
+template <bool FACES>
 __global__ void __launch_bounds__(FF_T) k_far_final(const double* part, int nchunk, const double* rhat, double dx,
-                                                    double dy, double dz, double k0, int faces, c128* F) {
+                                                    double dy, double dz, double k0, c128* F) {
   const int dir = blockIdx.x;
   double acc[6] = {0, 0, 0, 0, 0, 0};
   for (int c = threadIdx.x; c < nchunk; c += FF_T) {
@@ -194,7 +231,7 @@ __global__ void __launch_bounds__(FF_T) k_far_final(const double* part, int nchu
     double fr[3], fi[3];
     for (int q = 0; q < 3; ++q) {
       double hs = 0.0, hc = 1.0;   // half-cell phase of the component
-      if (faces) sincos(0.5 * k0 * r[q] * d[q], &hs, &hc);
+      if constexpr (FACES) sincos(0.5 * k0 * r[q] * d[q], &hs, &hc);
       fr[q] = (acc[2 * q] * hc - acc[2 * q + 1] * hs) * dV;
       fi[q] = (acc[2 * q] * hs + acc[2 * q + 1] * hc) * dV;
     }
@@ -204,23 +241,44 @@ __global__ void __launch_bounds__(FF_T) k_far_final(const double* part, int nchu
   }
 }
 
-// The split of one grid: padded mirror pairs, x parts, row tiles and
-// workgroups per direction block, doubles of scratch per direction.
+// The split of one grid and direction count: padded mirror pairs, x parts, row
+// tiles and workgroups per direction block, or the direct sum's chunks; doubles
+// of scratch per direction.
+//
+// The direct sum is taken where it is faster, by what the two were measured to
+// take (us, on an idle GPU; rounds of 512 workgroups, and what the other
+// wavefronts of a direction block add to the first).  Direct / product:
+//   5x4x6        1 direction 9.6 / 12.3; 361 10.3 / 15.3
+//   16x16x16     1 12.9 / 14.3; 181 15.5 / 15.9; 361 19.8 / 16.7
+//   32x32x32     1 13.1 / 16.6; 32 15.7 / 16.8; 48 19.0 / 17.1
+//   64x64x64     1 13.6 / 21.4; 8 21.5 / 21.7; 16 32.6 / 21.8
+//   128x128x32   1 13.7 / 22.4; 4 20.9 / 22.6; 8 32.4 / 22.9
+//   256x256x64   1 41 / 136; 4 125 / 136; 8 236 / 137
+//   1x256x256    1 13.5 / 48.1; 128 53.3 / 59.3; 181 72.0 / 66.0; 361 136 / 173
+//   2x200x200    1 13.6 / 35.5; 64 38.1 / 40.7; 96 51.7 / 41.1; 361 164 / 128
 struct FarShape {
   int jn, xparts, per, parts;
+  bool direct;
   int64_t scratch;
-  FarShape(int nx, int ny, int nz) {
+  FarShape(int nx, int ny, int nz, int ndir) {
     jn = ((nx + 1) / 2 + 3) / 4 * 4;
     xparts = (jn + FF_J - 1) / FF_J;
     const int64_t tiles = ((int64_t)ny * nz + FF_ROWS - 1) / FF_ROWS;
     per = (int)((tiles * xparts + FF_PARTS - 1) / FF_PARTS);
     parts = (int)((tiles + per - 1) / per) * xparts;
-    scratch = 2 * ((int64_t)jn + ny + nz) + 6 * (int64_t)parts;
+    const int64_t nv = (int64_t)nx * ny * nz, chunks = (nv + FF_CHUNK - 1) / FF_CHUNK;
+    const double waves = (ndir + FF_NT * 16 - 1) / (FF_NT * 16);
+    const double many = waves <= 4 ? 1 + (waves - 1) / 6 : 1.5 + 0.75 * (waves - 4);
+    const double t_product = 11.5 + (0.36 * std::min(jn, FF_J) * per + 4.2 * (per - 1)) * many;
+    const double t_direct = 11.0 + (nv < int64_t(1) << 21 ? 0.011 : 0.0138) * (double)(ndir * chunks);
+    direct = t_direct < t_product;
+    if (direct) parts = (int)chunks;
+    scratch = (direct ? 0 : 2 * ((int64_t)jn + ny + nz)) + 6 * (int64_t)parts;
   }
 };
 
 int64_t far_field_scratch(int nx, int ny, int nz, int ndir) {
-  return std::min<int64_t>(ndir * FarShape(nx, ny, nz).scratch, kFarScratchDoubles);
+  return std::min<int64_t>(ndir * FarShape(nx, ny, nz, ndir).scratch, kFarScratchDoubles);
 }
 
 int64_t far_field_scratch_doubles() { return kFarScratchDoubles; }
@@ -236,7 +294,7 @@ void* far_field_scratch_address() {
 void far_field(const c128* P, int nx, int ny, int nz, double dx, double dy, double dz, double k0, const double* rhat,
                int ndir, double* part, c128* F, hipStream_t s, bool faces) {
   if (ndir <= 0) return;
-  const FarShape f(nx, ny, nz);
+  const FarShape f(nx, ny, nz, ndir);
   // as many directions at a time as the scratch holds (a direction's result
   // does not depend on the others taken with it)
   const int most = (int)std::min<int64_t>(kFarScratchDoubles / f.scratch, 65535 * (int64_t)FF_DIRS);
@@ -245,13 +303,19 @@ void far_field(const c128* P, int nx, int ny, int nz, double dx, double dy, doub
   for (int d = 0; d < ndir; d += most) {
     const int n = std::min(most, ndir - d);
     const double* rd = rhat + 3 * (int64_t)d;
-    double* sums = part + 2 * (int64_t)tr * n;
-    hipLaunchKernelGGL(k_far_table, dim3((unsigned)(((int64_t)tr * n + FF_T - 1) / FF_T)), dim3(FF_T), 0, s, rd, n, nx, ny,
-                       nz, f.jn, dx, dy, dz, k0, part);
-    hipLaunchKernelGGL(k_far_partial, dim3((unsigned)f.parts, (unsigned)((n + FF_DIRS - 1) / FF_DIRS)), dim3(FF_T), 0, s,
-                       P, nx, ny, nz, n, f.jn, f.xparts, f.per, part, sums);
-    hipLaunchKernelGGL(k_far_final, dim3(n), dim3(FF_T), 0, s, sums, f.parts, rd, dx, dy, dz, k0, faces ? 1 : 0,
-                       F + 3 * (int64_t)d);
+    double* sums = part;
+    if (f.direct) {
+      hipLaunchKernelGGL(k_far_direct, dim3((unsigned)(n * f.parts)), dim3(FF_T), 0, s, P, nx, ny, nz, dx, dy, dz, k0, rd,
+                         f.parts, sums);
+    } else {
+      sums += 2 * (int64_t)tr * n;
+      hipLaunchKernelGGL(k_far_table, dim3((unsigned)(((int64_t)tr * n + FF_T - 1) / FF_T)), dim3(FF_T), 0, s, rd, n, nx,
+                         ny, nz, f.jn, dx, dy, dz, k0, part);
+      hipLaunchKernelGGL(k_far_partial, dim3((unsigned)f.parts, (unsigned)((n + FF_DIRS - 1) / FF_DIRS)), dim3(FF_T), 0, s,
+                         P, nx, ny, nz, n, f.jn, f.xparts, f.per, part, sums);
+    }
+    const auto final_kernel = faces ? k_far_final<true> : k_far_final<false>;
+    hipLaunchKernelGGL(final_kernel, dim3(n), dim3(FF_T), 0, s, sums, f.parts, rd, dx, dy, dz, k0, F + 3 * (int64_t)d);
     const hipError_t e = hipGetLastError();
     if (e != hipSuccess) throw std::runtime_error(std::string("far field launch: ") + hipGetErrorString(e));
   }
