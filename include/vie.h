@@ -381,7 +381,10 @@ vie_status vie_total_field_box(vie_problem* p, int32_t precision, const void* po
  * d_c / 2 along axis c), for
  * n_dir unit directions rhat (host, 3 doubles each; |rhat| = 1 within 1e-12
  * else VIE_EINVAL).  f_out: host, 3*n_dir complex.  FP64; synchronises the
- * stream. */
+ * stream.  In a context without a memory budget the problem keeps the call's
+ * device workspace (counted in footprint_bytes) and a pinned host copy of
+ * rhat and f_out until it is destroyed, where they take at most 16 MiB on the
+ * device; otherwise both last for the call.  The same holds for vie_rcs. */
 vie_status vie_far_field(vie_problem* p, const void* pol_dev, int32_t n_dir, const double* rhat, double* f_out,
                          void* stream);
 

@@ -2614,6 +2614,22 @@ extern "C++" {
 // Far-field workspace a problem may keep: the scratch's 8 MiB and room for
 // the directions and results of about 100 000.
 constexpr size_t kFarKeep = size_t(16) << 20;
+
+// A larger device workspace in place of the kept one (idle: every call waits
+// for its work), counted in the problem's footprint.
+static void keep_far_workspace(vie_problem& P, size_t bytes) {
+  auto count = [&](size_t was, size_t is) {
+    std::lock_guard<std::mutex> lk(P.ctx->mu);
+    P.ctx->used = P.ctx->used - std::min(P.ctx->used, was) + is;
+    P.footprint = P.footprint - std::min(P.footprint, was) + is;
+  };
+  const size_t old = P.far_dev.bytes;
+  P.far_dev.reset();
+  count(old, 0);
+  P.far_dev.alloc(bytes);
+  count(0, bytes);
+}
+
 static void far_field_host(vie_problem* p, const void* pol_dev, int32_t n_dir, const double* rhat,
                            std::vector<c128>& F, hipStream_t s) {
   if (!p || !pol_dev || !rhat) fail(VIE_EINVAL, "problem, pol and rhat are required");
@@ -2634,7 +2650,7 @@ static void far_field_host(vie_problem* p, const void* pol_dev, int32_t n_dir, c
   if (!keep)
     once.alloc(p_at + pb);
   else if (p->far_dev.bytes < p_at + pb)
-    p->far_dev.alloc(p_at + pb);   // every call waits for its work: the old one is idle
+    keep_far_workspace(*p, p_at + pb);
   char* dev = (keep ? p->far_dev : once).as<char>();
   if (keep && p->far_host_bytes < rb + fb) {
     ApiShared api;
@@ -2650,11 +2666,17 @@ static void far_field_host(vie_problem* p, const void* pol_dev, int32_t n_dir, c
   const bool pinned = keep && p->far_host_bytes >= rb + fb;
   F.resize(3 * (size_t)n_dir);
   if (pinned) std::memcpy((char*)p->far_host + fb, rhat, rb);
-  hip_check(hipMemcpyAsync(dev + r_at, pinned ? (const char*)p->far_host + fb : (const char*)rhat, rb, hipMemcpyHostToDevice, s),
-            "upload rhat");
-  vie::far_field((const c128*)pol_dev, g.nx, g.ny, g.nz, g.dx, g.dy, g.dz, p->k0, (const double*)(dev + r_at), n_dir,
-                 (double*)(dev + p_at), (c128*)dev, s, p->rooftop);
-  hip_check(hipMemcpyAsync(pinned ? p->far_host : (void*)F.data(), dev, fb, hipMemcpyDeviceToHost, s), "download F");
+  try {
+    hip_check(hipMemcpyAsync(dev + r_at, pinned ? (const char*)p->far_host + fb : (const char*)rhat, rb,
+                             hipMemcpyHostToDevice, s),
+              "upload rhat");
+    vie::far_field((const c128*)pol_dev, g.nx, g.ny, g.nz, g.dx, g.dy, g.dz, p->k0, (const double*)(dev + r_at), n_dir,
+                   (double*)(dev + p_at), (c128*)dev, s, p->rooftop);
+    hip_check(hipMemcpyAsync(pinned ? p->far_host : (void*)F.data(), dev, fb, hipMemcpyDeviceToHost, s), "download F");
+  } catch (...) {
+    (void)hipStreamSynchronize(s);   // what was enqueued still uses the buffers
+    throw;
+  }
   hip_check(hipStreamSynchronize(s), "far field");
   if (pinned) std::memcpy(F.data(), p->far_host, fb);
 }

@@ -48,3 +48,32 @@ def test_far_field(vie_ctx, shape, n_dir, rooftop):
             assert np.array_equal(f.cpu().numpy(), got)
     finally:
         Pr.close()
+
+
+def test_kept_workspace_is_in_the_footprint(vie_ctx):
+    """The device workspace that a problem keeps is counted and bounded by 16
+    MiB; a context with a memory budget keeps none."""
+    case = W.random_tiny(410, (24, 30, 20), fill=0.8)
+    grid = V.make_grid(case.nx, case.ny, case.nz, case.dx, case.dy, case.dz, case.wavelength)
+    rng = np.random.default_rng(411)
+    d = rng.standard_normal((400, 3))
+    d /= np.linalg.norm(d, axis=1, keepdims=True)
+    budgeted = V.vie_context_create(0, 4 << 30)
+    try:
+        for ctx in (vie_ctx, budgeted):
+            P = V.Problem(grid, case.eps, None, 0, ctx=ctx)
+            try:
+                x = torch.ones(P.shape, dtype=torch.complex128, device="cuda")
+                sizes = [P.info().footprint_bytes]
+                for n in (1, 400, 7, 400):
+                    V.vie_far_field(P.handle, x, d[:n])
+                    sizes.append(P.info().footprint_bytes)
+                kept = [s - sizes[0] for s in sizes[1:]]
+                if ctx == budgeted:
+                    assert kept == [0, 0, 0, 0]
+                else:
+                    assert 9 * 8 <= kept[0] < kept[1] == kept[2] == kept[3] <= 16 << 20 and kept[1] >= 400 * 9 * 8
+            finally:
+                P.close()
+    finally:
+        V.vie_context_destroy(budgeted)
