@@ -41,9 +41,20 @@ CSRC = os.path.join(ROOT, "paper_2501_13512_amd", "csrc")
 COPY_BYTES = 512 * 1024 * 1024
 
 
+def kernel_sources():
+    """The product's translation units and every header of csrc they include."""
+    todo, seen = ["mvm.hip", "zconv32.hip", "zconv64.hip"], []
+    while todo:
+        f = todo.pop(0)
+        if f not in seen:
+            seen.append(f)
+            todo += re.findall(r'#include "(\w+\.h)"', open(os.path.join(CSRC, f)).read())
+    return sorted(seen)
+
+
 def kernel_hash() -> str:
     h = hashlib.sha256()
-    for f in ("mvm.hip", "fft_core.h", "cx.h"):
+    for f in kernel_sources():
         h.update(open(os.path.join(CSRC, f), "rb").read())
     return h.hexdigest()[:16]
 
