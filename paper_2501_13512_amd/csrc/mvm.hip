@@ -926,25 +926,27 @@ void mvm(const MvmBatch<R>& b, const c128* x, c128* y, bool mask_input, hipStrea
 // The z-pass variant of a shape; `cols` counts the columns of every system of
 // the batch.  The lines lie where two variants cross.  Measured on 1024 to
 // 262144 columns with the kernels alone, 5 us of event overhead with them (us;
-// on either side of each line, the variant taken first):
+// on either side of each line, the variant taken first), and checked with
+// products of one problem repeated and of several in turn:
 //    32: f32 16384 V2 11.1, V4 11.4; f64 16384 V4 16.0, V2 16.2, 24576 V2 16.1, V4 17.1; f64 rooftop
 //        98304 V4 38.3, V2 39.2, 147456 V2 52.6, V4 53.6
 //    36: f32 V2 (9216: 10.8, V4 13.1); f64 1024 V2 7.2, V4 7.7, 6144 V4 11.9, V2 12.2,
 //        36864 V3 30.3, V4 30.8, 147456 V3 98.9, V4 109
 //    48: 3072 f32 V0 8.5, V2 9.1, f64 V4 11.2, V2 11.5; 6144 f32 V2 10.4, V0 10.9, f64 V2 14.3, V4 16.7
-//    64: f32 V2 (1024: 7.1, V4 7.6; 65536: 31.8, 32.9; 98304: 43.1, 45.2), 147456 V4 84.4, V2 90.7;
-//        f64 V4 (V2 within 1%)
+//    64: V4 (f32 98304: V2 43.1, V4 45.2 with the spectrum in the caches, but 192x128x32 products of
+//        several problems in turn 157, 153; f64 V2 within 1%)
 //    72: f32 V2 (65536: 43, V3 57; 262144: 242, V3 253); f64 4096 V0 12.9, V2 13.4, 6144 V2 16.9, V0 18.8,
 //        196608 V2 296, V3 314, 262144 V3 465, V2 504; f64 rooftop 16384 V2, 24576 V3 34.0, V2 35.5
-//    96: 3072 V0, 6144 f64 V2 18.8, V0 19.8; 147456 f64 V2 289, V4 311, 196608 f64 V4 429, V2 449;
+//    96: 6144 f32 V0 14.9, V2 15.2, f64 V2 18.8, V0 19.8; 147456 f64 V2 289, V4 311, 196608 f64 V4 429, V2 449;
 //        196608 f32 V2 210, V4 218, 262144 f32 V4 311, V2 334
 //   128: 3072 V4 15.6, V2 16.7 (f64), 6144 V2 19.1, V4 20.3; 73728 f32 V2 95.4, V4 93.5, 98304 f32 V4 124,
 //        V2 129; f32 rooftop 196608 V2 200, V4 219, 262144 V4 330, V2 338; f64 V2 (196608: 457, V4 532)
 //   144: f32 36864 V4 55.3, V2 56.9, 65536 V2 113, V4 118, 196608 V2 305, V4 329; f64 V2 (65536: 206, V3 263)
 //   192: f32 V4 (65536: 157, V2 168); f64 V2 (1024: 13.2, V4 13.9; 262144: 1428, V4 1560)
-//   256: f32 V4 (16384: 45.5, V2 48.0); f64 196608 V2 1135, V4 1187, 262144 V4 1755, V2 1810
+//   256: f32 V4 (16384: 45.5, V2 48.0); f64 V2 (196608: 1135, V4 1187), 256x256x128 products V4 3406, V2 3477,
+//        rooftop V2 3147, V4 3267
 //   from 288 on V4 (f64 288: V4 33.8, V2 39.1 at 4096 columns)
-// Tiles of half a cache line (V2 of 96, f32 128, f64 72 and 256) rely on both
+// Tiles of half a cache line (V2 of 96, f32 128, f64 72) rely on both
 // halves of a line meeting in the caches, so they end where the work buffer
 // leaves the Infinity Cache.  Below 32 V0 and V4 are one.  The mirror columns
 // (V1) were ahead in none of 96 shapes of lengths 4 to 256.
@@ -955,15 +957,15 @@ int zpass_rule(int elem_bytes, int lz, bool rooftop, int64_t cols) {
     case 32: return cols < (f32 ? 16384 : rooftop ? 131072 : 20480) ? 4 : 2;
     case 36: return f32 || cols < 4096 ? 2 : (cols >= 32768 ? 3 : 4);
     case 48: return cols >= 5120 ? 2 : (f32 ? 0 : 4);
-    case 64: return f32 && cols < 131072 ? 2 : 4;
+    case 64: return 4;
     case 72:
       if (f32) return 2;
       if (cols < 5120) return 0;
       return cols >= (rooftop ? 20480 : 229376) ? 3 : 2;
-    case 96: return cols < 5120 ? 0 : (cols >= (f32 ? 229376 : 172032) ? 4 : 2);
+    case 96: return cols < (f32 ? 8192 : 5120) ? 0 : (cols >= (f32 || rooftop ? 229376 : 172032) ? 4 : 2);
     case 128: return cols < 5120 || (f32 && cols >= (rooftop ? 229376 : 80000)) ? 4 : 2;
     case 144: return f32 && cols < 57344 ? 4 : 2;
-    case 256: return f32 || cols >= 229376 ? 4 : 2;
+    case 256: return f32 || (!rooftop && cols >= 229376) ? 4 : 2;
     default: return f32 || lz >= 288 ? 4 : 2;
   }
 }
