@@ -100,7 +100,7 @@ def mvm_profile(V, handle, info, nx, ny, nz, prec, reps, rooftop=False):
     return {"ms": float(np.sum(ms)), "algorithmic_GBps": sum(pb) / (float(np.sum(ms)) * 1e-3) / 1e9,
             "pass_ms": [float(v) for v in ms], "pass_bytes": pb, "pass_names": names,
             "pass_GBps": [b / (m * 1e-3) / 1e9 for b, m in zip(pb, ms)],
-            "zpass_variant": zvar, "zpass_tune_ms": [round(float(v), 4) for v in info.zpass_tune_ms[q]],
+            "zpass_variant": zvar,
             "dominant": {"kernel": names[dom], "achieved": achieved, "bytes": pb[dom], "ms": float(ms[dom])}}
 
 

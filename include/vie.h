@@ -175,10 +175,10 @@ typedef struct {
   int64_t footprint_bytes;    /* device memory held by the problem */
   int32_t n_block_solver_groups;  /* groups solved one workgroup per block */
   int32_t zpass_variant[2];   /* z-pass kernel picked for the full-grid product [FP64, MIXED] */
-  float zpass_tune_ms[2][5];  /* time per z-pass variant (-1 = not timed: variants are picked by shape) */
+  float zpass_tune_ms[2][5];  /* always -1: variants are picked by shape, not timed */
   int32_t plane_variant[2];   /* plane-kernel variant picked for the full-grid product [FP64, MIXED]
-                                 (0 when its transforms are not square and small enough) */
-  float plane_tune_ms[2][3];  /* time per plane variant (-1 = not timed: variants are picked by shape) */
+                                 (0 when its transforms are not square and at most 64) */
+  float plane_tune_ms[2][3];  /* always -1, as zpass_tune_ms */
 } vie_problem_info;
 
 /* One shape group of a block plan: blocks whose bounding boxes share FFT
@@ -265,24 +265,26 @@ vie_status vie_problem_create_rooftop(vie_context* ctx, const vie_grid* grid, co
 vie_status vie_problem_destroy(vie_problem* p);
 vie_status vie_problem_get_info(const vie_problem* p, vie_problem_info* info);
 
-/* Pins the z-pass kernel variant (0-4; 1 = mirror columns; lengths below
- * 32 use 0 for 2-4) of every FFT product of
- * the problem in one precision, full-grid and block products alike; -1
- * restores the choice by shape.  For kernel studies and a reproducible
- * kernel choice: the variants compute the same transform (results agree to
- * rounding; tested).  Synchronises the device; call it while no work of the
- * problem is in flight.  Errors: VIE_EINVAL for a bad precision or
- * variant. */
+/* Pins the z-pass kernel variant (0-4; 1 = mirror columns) of every FFT
+ * product of the problem in one precision, full-grid and block products
+ * alike; -1 restores the choice by shape.  Lengths below 32 use 0 for 2-4,
+ * lengths from 288 on use 4 for 2 and 3, and length 192 in FP32 uses 4 for 2.
+ * For kernel studies and a reproducible kernel choice: the variants compute
+ * the same transform (0, 2, 3 and 4 bit for bit, 1 to rounding; tested).
+ * Synchronises the device; call it while no work of the problem is in
+ * flight.  Errors: VIE_EINVAL for a bad precision or variant. */
 vie_status vie_problem_set_zpass(vie_problem* p, int32_t precision, int32_t variant);
 
 /* Pins the plane-kernel variant of every FFT product of the problem in one
- * precision (products whose x and y lengths are equal and at most 64 run
- * the x and y transforms of a z-plane in one kernel; the variants differ in
- * the planes one workgroup takes: 0 as many as 48 KB of LDS hold, at most
- * 16; 1 at most two; 2 one); -1 restores the choice by shape.  Same
- * transform, results agree to rounding (tested).  Synchronises the device;
- * call it while no work of the problem is in flight.  Errors: VIE_EINVAL
- * for a bad precision or variant. */
+ * precision; -1 restores the choice by shape.  Products whose x and y lengths
+ * are equal run the x and y transforms of a z-plane in one kernel: always up
+ * to length 64, at 96 and (MIXED) 128 where the plane count suits it.  Up to
+ * 64 the variants differ in the planes one workgroup takes: 0 as many as 48
+ * KB of LDS hold, at most 16; 1 at most two, from length 48 on one by 512
+ * threads; 2 one by 256.  At 96 and 128 all are one plane by 1024 threads and
+ * a pinned variant changes nothing.  Same transform, results agree to
+ * rounding (tested).  Synchronises the device; call it while no work of the
+ * problem is in flight.  Errors: VIE_EINVAL for a bad precision or variant. */
 vie_status vie_problem_set_plane(vie_problem* p, int32_t precision, int32_t variant);
 
 /* The block plan that vie_problem_create_overlap would build for these

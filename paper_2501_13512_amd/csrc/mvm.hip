@@ -295,16 +295,16 @@ __global__ void __launch_bounds__((Geo<R, L>::T * Geo<R, L>::ROWP)) k_row_inv_lo
 }
 
 // ------------------------------------------------------------------ plane passes
-// Small square transforms (lx = ly <= 128): the x and y transforms of a
+// Square transforms (lx = ly <= 128, plane_supported): the x and y transforms of a
 // z-plane run in one kernel with the plane in LDS, so passes 1 + 2 become
 // k_plane_fwd and passes 4 + 5 become k_plane_inv_local (one launch and one
 // trip through HBM fewer each way; same BiCGSTAB fusion as the row kernels).
 // A workgroup takes NPL consecutive planes (c, z) of one system; LDS holds
 // them as [NPL][L][L + 1] (rows padded against bank conflicts on columns).
 // Variant PV sets NPL: 0 as many planes as 48 KB of LDS hold (at most 16),
-// 1 at most two (from 48 on one plane with twice the threads), 2 one plane.  From 96 on a workgroup is 1024 threads and one
-// plane, the CU's LDS holding no second FP64 one.  Fewer planes per workgroup mean more, shorter
-// workgroups: the product's latency falls when few systems are active (two
+// 1 at most two (from 48 on one plane with twice the threads), 2 one plane.
+// From 96 on every variant is one plane by 1024 threads, the CU's LDS holding
+// no second FP64 one.  Fewer planes per workgroup mean more, shorter workgroups: the product's latency falls when few systems are active (two
 // 32 x 32 planes of a 16 x 16 box take 3 transform rounds of 32 pencils
 // where five planes take 8), at the cost of more workgroups to dispatch.
 template <typename R, int L, int PV>

@@ -46,9 +46,11 @@ __device__ __forceinline__ FoldCol fold_col(int f, int m, int L) {
 //      cache line or more, with no more threads to a column than its first
 //      radix keeps busy.  The pass waits on memory, LDS and barriers in
 //      turn, so many small workgroups at different points of it hide more
-//      than few large ones (see zpass_rule for the times).
+//      than few large ones (see zpass_rule for the times; 144 in FP32 has a
+//      geometry of its own, LINE2)
 //   3: one cache line of columns, min_butterflies threads, prefetch
 //   4: one cache line of columns, max_butterflies threads
+// zcol_kernel has the lengths at which variants share a kernel.
 template <typename R, int LZ, int V, int K>
 struct ZColGeo {
   static constexpr int T = PlanInfo<LZ>::max_butterflies;
