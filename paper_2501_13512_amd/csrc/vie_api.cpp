@@ -2674,7 +2674,8 @@ static void far_field_host(vie_problem* p, const void* pol_dev, int32_t n_dir, c
                    (double*)(dev + p_at), (c128*)dev, s, p->rooftop);
     hip_check(hipMemcpyAsync(pinned ? p->far_host : (void*)F.data(), dev, fb, hipMemcpyDeviceToHost, s), "download F");
   } catch (...) {
-    (void)hipStreamSynchronize(s);   // what was enqueued still uses the buffers
+    // what was enqueued still uses the buffers
+    if (hipStreamSynchronize(s) != hipSuccess) (void)hipGetLastError();
     throw;
   }
   hip_check(hipStreamSynchronize(s), "far field");
